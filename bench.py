@@ -246,7 +246,7 @@ def gpu_clocks():
         return {"unavailable": type(e).__name__}
 
 
-KERNELS = ["phsa_compress", "phsa_select_split", "phsa_select", "phsa_index_count", "phsa_index_scan_tiles", "phsa_index_scan_lists",
+KERNELS = ["phsa_compress", "phsa_select_split", "phsa_select", "phsa_index_count", "phsa_index_scan",
            "phsa_index_fill", "phsa_attn_fwd_sparse", "phsa_attn_fwd_band", "phsa_attn_fwd_combine",
            "phsa_attn_bwd_pre", "phsa_attn_bwd_band_dkv_init", "phsa_attn_bwd_band_init_reduce", "phsa_attn_bwd_band_dkv",
            "phsa_attn_bwd_band_dq", "phsa_attn_bwd_sparse",
@@ -357,12 +357,11 @@ def bench_train(steps: int, warmup: int, seed: int, name: str = "train_32k"):
     # pair gathers its query rows (and dO rows) and leaves a bf16 partial (plus
     # the forward's (m, l)); every work unit loads its K/V tile once.  This is
     # the schedule's own traffic floor, above the method's algorithmic minimum.
-    unit_tokens = 64 * (64 // G)
+    unit_tokens, unit_fwd = 64 * (64 // G), 512   # list entries per work unit, backward and forward
     T64 = L // 64
-    units = B * Hkv * T64 + ntile // unit_tokens
-    kv_bytes = units * 64 * d * 2 * 2
+    kv_fwd, kv_bytes = ((B * Hkv * T64 + ntile // u) * 64 * d * 2 * 2 for u in (unit_fwd, unit_tokens))
     pair_row = G * d * 2
-    design_bytes = {"phsa_attn_fwd_sparse": ntile * (2 * pair_row + G * 8 + 4) + kv_bytes,
+    design_bytes = {"phsa_attn_fwd_sparse": ntile * (2 * pair_row + G * 8 + 4) + kv_fwd,
                     "phsa_attn_bwd_sparse": ntile * (3 * pair_row + G * 8 + 4) + kv_bytes + B * L * Hkv * d * 2 * 2}
     bytes_compress = B * L * Hkv * d * 2 + B * L + B * Hkv * T * d * 4
     bytes_select = B * L * Hq * d * 2 + B * Hkv * T * d * 4 + B * Hkv * L * wl.ksel * 4

@@ -16,17 +16,37 @@ namespace {
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 
+// Sizes of the attention work units (list entries per workgroup).
+//   Backward: a unit is a whole list up to 64 chunks of 64 MFMA rows, so that
+//   long lists write their float32 dK/dV once; a problem with few entries gets
+//   shorter units, because one workgroup walking a list that every row is on
+//   (block 0) is otherwise the kernel's whole duration.
+//   Forward: a unit writes nothing per block, so units are short: at most 512
+//   entries, fewer in small problems.
+// kFill: workgroups that should share the entries, four rounds of the resident
+// ones (256 CUs x 2 backward, x 3 forward).  Half or twice as many: within 2%
+// forward at 8k and 16k; backward at 6 x 2112 tokens, 24 KV groups of 4 heads,
+// sparse kernel and finalize take 166 us with 2048, 162 with 3072 and 173 with
+// 4096, and the dK/dV partials grow with it.
+constexpr int64_t kFillBwd = 2048, kFillFwd = 3072;
+inline int unit_size(int64_t entries, int64_t fill, int step, int most) {
+  const int64_t want = (entries + fill - 1) / fill;
+  return (int)std::min<int64_t>(most, std::max<int64_t>(1, (want + step - 1) / step) * step);
+}
+
 // Carves the inverted-index workspace starting at `base` (NULL = size only).
 size_t index_layout(const Geom &g, char *base, IndexWs *ix) {
   IndexWs w{};
   const int64_t R = (int64_t)g.B * g.Hkv;
   const int64_t nbgt = R * g.T;
+  const int nsp = g.ksel - g.band;  // list entries per row at most; a band geometry keeps one slot for the band partial
   w.W = (g.Lq + kIndexTile - 1) / kIndexTile;
-  w.unit_tokens = 64 * (64 / g.G);  // 64 chunks of 64 MFMA rows
-  w.nnz_max = R * g.Lq * (g.ksel - g.band);  // a band geometry keeps one slot per row for the band partial
+  w.nnz_max = R * g.Lq * nsp;
   w.band_base = w.nnz_max;
-  w.discard = (w.nnz_max + (g.band ? R * g.Lq : 0)) * g.G;
-  w.units_max = nbgt + (w.nnz_max + w.unit_tokens - 1) / w.unit_tokens;
+  w.unit_tokens = unit_size(w.nnz_max, kFillBwd, 128 / g.G, 64 * (64 / g.G));
+  w.units_bg = g.T + (int)(((int64_t)g.Lq * nsp + w.unit_tokens - 1) / w.unit_tokens);
+  w.fpart = unit_size(w.nnz_max, kFillFwd, 64 / g.G, 512);
+  w.funits_bg = g.T + (int)(((int64_t)g.Lq * nsp + w.fpart - 1) / w.fpart);
   size_t off = 0;
   auto take = [&](size_t bytes) {
     char *p = base ? base + off : nullptr;
@@ -34,15 +54,18 @@ size_t index_layout(const Geom &g, char *base, IndexWs *ix) {
     return p;
   };
   w.cntw = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * R * w.W * g.T));
+  w.toff = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * R * w.W * g.T));
   w.cnt = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * nbgt));
-  w.off = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * (nbgt + 1)));
-  w.uoff = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * (nbgt + 1)));
-  w.totals = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * 4));
-  w.wsum = reinterpret_cast<int4 *>(take(sizeof(int4) * ((nbgt + 255) / 256)));
+  w.off = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * nbgt));
+  w.uoff = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * (nbgt + R)));
+  w.ucnt = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * R));
+  w.nfin = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * R));
   w.fin = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * nbgt));
+  w.fcnt = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * R));
   w.tok = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * w.nnz_max));
   w.pmap = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * R * g.Lq * g.ksel));  // every slot, band slot too
-  w.units = reinterpret_cast<int2 *>(take(sizeof(int2) * w.units_max));
+  w.units = reinterpret_cast<int4 *>(take(sizeof(int4) * R * w.units_bg));
+  w.funits = reinterpret_cast<int2 *>(take(sizeof(int2) * R * w.funits_bg));
   if (ix) *ix = w;
   return off;
 }
@@ -122,10 +145,9 @@ size_t fwd_layout(const Geom &g0, char *base, FwdWs *ws) {
   const Geom &g = w.co.gc;
   off += index_layout(g, base ? base + off : nullptr, &w.ix);
   w.ix.bflag = w.co.bflag;
-  // partials in list order, one per (entry, head), then the band partials (a
-  // band geometry), then one discard row that absorbs the stores of rows past
-  // the end of a chunk
-  const int64_t slots = w.ix.discard + 1;
+  // partials in list order, one per (entry, head); a band row's own partial
+  // stays in its merging workgroup
+  const int64_t slots = w.ix.nnz_max * g.G;
   w.opart = base ? base + off : nullptr;
   off += align_up(slots * g.d * elem_bytes(g));
   w.ml = base ? reinterpret_cast<float2 *>(base + off) : nullptr;
@@ -147,11 +169,11 @@ size_t bwd_layout(const Geom &g0, char *base, BwdWs *ws) {
   w.Dvec = base ? reinterpret_cast<float *>(base + off) : nullptr;
   off += align_up(sizeof(float) * (size_t)g.B * g.Hq * g.Lq);
   if (g.dtype == PHSA_BF16) {
-    const int64_t slots = w.ix.discard + 1;  // list and band partials + the discard row
+    const int64_t slots = w.ix.nnz_max * g.G;
     w.dqpart = base ? base + off : nullptr;
     off += align_up(slots * g.d * elem_bytes(g));
     w.dkvpart = base ? reinterpret_cast<float *>(base + off) : nullptr;
-    off += align_up(sizeof(float) * (size_t)w.ix.units_max * 2 * 64 * g.d);
+    off += align_up(sizeof(float) * (size_t)g.B * g.Hkv * w.ix.units_bg * 2 * 64 * g.d);
     if (g.band) {
       w.bkv = base ? reinterpret_cast<float *>(base + off) : nullptr;
       off += align_up(sizeof(float) * (size_t)g.B * g.Hkv * g.T * 2 * 64 * g.d);

@@ -119,20 +119,17 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_sparse_kernel(
   __shared__ __attribute__((aligned(16))) float dd_s[64];
   __shared__ __attribute__((aligned(16))) int pos_s[64];
 
-  const int u = blockIdx.x;
-  if (u >= ix.totals[1]) return;
-  const int2 unit = ix.units[u];
-  const int bgt = unit.x, e0 = unit.y;
-  const int cnt = ix.cnt[bgt];
-  const int n_ent = min(cnt - e0, ix.unit_tokens);
-  const bool whole_block = (e0 == 0) && (n_ent == cnt);
+  const int u = xcd_item(blockIdx.x, gridDim.x);  // the units of one list on one XCD
+  // the unit's record is read beside the count that tells whether it exists
+  const int4 unit = ix.units[u];
+  if (u % ix.units_bg >= ix.ucnt[u / ix.units_bg]) return;
+  const int bgt = unit.x, n_ent = unit.y;
+  const bool whole_block = unit.w;
   const int bg = bgt / gm.T, t = bgt - bg * gm.T;
   const int b = bg / gm.Hkv, g = bg - b * gm.Hkv;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l16 = lane & 15, q4 = lane >> 4, kq = q4 * 8;
-  // list position of the unit's first entry, read once (a load inside the chunk loop
-  // would make the wait for it also wait for the prefetched rows)
-  const int64_t list0 = (int64_t)ix.off[bgt] + e0;
+  const int64_t list0 = unit.z;  // list position of the unit's first entry
   const int32_t *list = ix.tok + list0;
   const int64_t krow0 = ((int64_t)b * gm.Lk + (int64_t)t * 64) * gm.Hkv + g;  // global row of key 0
   // the group's first head of sequence b; a row's head h, query i is at i * Hq * D + (h - gG) * D
@@ -141,12 +138,6 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_sparse_kernel(
   const float *lse_b = LSE + ((int64_t)b * gm.Hq + g * G) * gm.Lq;  // [G][Lq] of the group
   const float *dd_b = Dvec + (int64_t)b * gm.Lq * gm.Hq + g * G;     // [Lq][Hq] from the group's first head
 
-  for (int x = tid; x < 64 * VPR; x += 256) {
-    const int kk = x / VPR, c = (x % VPR) * 8;
-    const int64_t src = (krow0 + (int64_t)kk * gm.Hkv) * D + c;
-    *reinterpret_cast<uint4 *>(&Ks[kk * KPQ + c]) = *reinterpret_cast<const uint4 *>(K + src);
-    *reinterpret_cast<uint4 *>(&Vs[swz<D>(kk, c)]) = *reinterpret_cast<const uint4 *>(V + src);
-  }
   // dK^T / dV^T accumulators: lane (q, j) holds feature 16nt + 4q + r of key 16w + j
   f32x4 dkt[NT], dvt[NT];
 #pragma unroll
@@ -190,14 +181,38 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_sparse_kernel(
       }
     }
   };
+  // the first entries, the K/V tile and the first rows, each group issued
+  // before the one ahead of it is waited for
   load_entries(0);
-  fetch_rows();
-  load_entries(CT);
+  __builtin_amdgcn_sched_barrier(0);
+  {
+    u32x4 kr[NV], vr[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      const int x = tid + 256 * k, kk = x / VPR, c = (x % VPR) * 8;
+      const int64_t src = (krow0 + (int64_t)kk * gm.Hkv) * D + c;
+      kr[k] = *reinterpret_cast<const u32x4 *>(K + src);
+      vr[k] = *reinterpret_cast<const u32x4 *>(V + src);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    fetch_rows();
+    load_entries(CT);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      const int x = tid + 256 * k, kk = x / VPR, c = (x % VPR) * 8;
+      *reinterpret_cast<u32x4 *>(&Ks[kk * KPQ + c]) = kr[k];
+      *reinterpret_cast<u32x4 *>(&Vs[swz<D>(kk, c)]) = vr[k];
+    }
+  }
 
   const float sl2 = gm.scale * kLog2e;
   const float lsc = __log2f(gm.scale);       // P' = scale * P
   const float inv_scale = 1.f / gm.scale;
   const int key = t * 64 + wave * 16 + l16;  // the key whose S column this lane holds
+  // the unit's dQ partials as a buffer that ends with it: stores of rows past
+  // the list fall outside and are dropped
+  const auto qbuf = __builtin_amdgcn_make_buffer_rsrc(dqpart + list0 * G * D, 0, n_ent * G * D * 2, 0x00020000);
 
   for (int c0 = 0; c0 < n_ent; c0 += CT) {
     __syncthreads();  // previous chunk is done with Qs, dOs, dSt and the row tables
@@ -288,19 +303,13 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_sparse_kernel(
       *reinterpret_cast<uint2 *>(&Qs[row * KPQ + nt * 16 + q4 * 4]) = *reinterpret_cast<const uint2 *>(o4);
     }
     wave_lds_sync();
-    {
-      const int64_t run0 = (list0 + c0) * G + wave * 16;  // first row of this wave
-      const int nrows = min(CT, n_ent - c0) * G - wave * 16;                // valid rows of this wave
-      // every lane stores (rows past the chunk's end go to the discard row), so the
-      // number of stores per chunk is fixed and the waits for the prefetched rows
-      // need not wait for them
-      const int64_t discard = ix.discard;
+    // every lane stores, so the number of stores per chunk is fixed and the
+    // waits for the prefetched rows need not wait for them
 #pragma unroll
-      for (int k = 0; k < 16 * VPR / 64; ++k) {
-        const int v = lane + 64 * k, r = v / VPR, cc = (v % VPR) * 8;
-        const int64_t row = r < nrows ? run0 + r : discard;
-        st_stream16(dqpart + row * D + cc, &Qs[(wave * 16 + r) * KPQ + cc]);
-      }
+    for (int k = 0; k < 16 * VPR / 64; ++k) {
+      const int v = lane + 64 * k, r = v / VPR, cc = (v % VPR) * 8;
+      __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4 *>(&Qs[(wave * 16 + r) * KPQ + cc]), qbuf,
+                                             ((c0 * G + wave * 16 + r) * D + cc) * 2, 0, 2);
     }
   }
 
@@ -348,8 +357,8 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_sparse_kernel(
 // units): sum the float32 partials of its units, or zeros for a block nobody
 // selected; a band geometry adds the band's float32 dK/dV of the tile (bkv).
 // Each block's 2 x 64 x d outputs are split over kFinSplit workgroups; each
-// thread owns 4 consecutive features (16-byte loads).  A fixed grid of
-// kFinGrid x kFinSplit workgroups walks the list, kFinGrid blocks apart.
+// thread owns 4 consecutive features (16-byte loads).  A fixed grid of about
+// kFinGrid x kFinSplit workgroups walks the lists, each in one (b, g).
 constexpr int kFinSplit = 16;
 constexpr int kFinGrid = 512;
 template <int D>
@@ -357,10 +366,11 @@ __global__ __launch_bounds__(256) void dkv_finalize_kernel(const float *__restri
                                                            const float *__restrict__ bkv, bf16_t *__restrict__ dK,
                                                            bf16_t *__restrict__ dV, Geom gm, IndexWs ix) {
   constexpr int PER = 64 * D / kFinSplit;  // elements of dK (and of dV) per workgroup
-  for (int j = blockIdx.x; j < ix.totals[2]; j += gridDim.x) {
-    const int bgt = ix.fin[j];
-    const int u0 = ix.uoff[bgt], u1 = ix.uoff[bgt + 1];
-    const int bg = bgt / gm.T, t = bgt - bg * gm.T;
+  const int R = gm.B * gm.Hkv, bg = blockIdx.x % R;
+  for (int j = blockIdx.x / R; j < ix.nfin[bg]; j += gridDim.x / R) {
+    const int bgt = ix.fin[bg * gm.T + j], t = bgt - bg * gm.T;
+    const int32_t *uo = ix.uoff + (int64_t)bg * (gm.T + 1) + t;
+    const int u0 = bg * ix.units_bg + uo[0], u1 = bg * ix.units_bg + uo[1];
     const int b = bg / gm.Hkv, g = bg - b * gm.Hkv;
     for (int x = blockIdx.y * PER + threadIdx.x * 4; x < (int)(blockIdx.y + 1) * PER; x += 256 * 4) {
       const int kk = x / D, c = x - kk * D;
@@ -444,14 +454,15 @@ static hipError_t launch_bwd_t(const Geom &g, const void *Q, const void *K, cons
     if (e != hipSuccess) return e;
   }
   const float *bk = g.band ? bkv : nullptr;
+  const int R = g.B * g.Hkv;
   timing_begin("phsa_attn_bwd_sparse", s);
-  hipLaunchKernelGGL((attn_bwd_sparse_kernel<D, G>), dim3((unsigned)ix.units_max), dim3(256), 0, s,
+  hipLaunchKernelGGL((attn_bwd_sparse_kernel<D, G>), dim3((unsigned)(g.B * g.Hkv * ix.units_bg)), dim3(256), 0, s,
                      static_cast<const bf16_t *>(Q), static_cast<const bf16_t *>(K), static_cast<const bf16_t *>(V),
                      static_cast<const bf16_t *>(dO), LSE, Dvec, g, ix, static_cast<bf16_t *>(dqpart),
                      static_cast<bf16_t *>(dK), static_cast<bf16_t *>(dV), dkvpart, bk);
   timing_end(s);
   timing_begin("phsa_attn_bwd_dkv_finalize", s);
-  hipLaunchKernelGGL((dkv_finalize_kernel<D>), dim3(std::min(g.B * g.Hkv * g.T, kFinGrid), kFinSplit), dim3(256), 0, s,
+  hipLaunchKernelGGL((dkv_finalize_kernel<D>), dim3(R * std::min(g.T, std::max(1, kFinGrid / R)), kFinSplit), dim3(256), 0, s,
                      dkvpart, bk,
                      static_cast<bf16_t *>(dK), static_cast<bf16_t *>(dV), g, ix);
   timing_end(s);

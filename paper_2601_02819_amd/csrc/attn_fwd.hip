@@ -2,10 +2,10 @@
 //
 // Work is key-block-major.  Every query row selects its own blocks, so the
 // only operand that many rows share is a key/value block.  A workgroup takes
-// one work unit = one (b, g, t) block plus up to unit_tokens entries of the
-// list of rows that selected it and keeps K_t and V_t in LDS.  Each wave then
-// works through the unit on its own, in wave chunks of 16 MFMA rows (16 / G
-// tokens x the G heads of the group), chunks w, w + 4, ...:
+// one work unit = one (b, g, t) block plus up to fpart entries of the list of
+// rows that selected it and keeps K_t and V_t in LDS.  Each wave then works
+// through the unit on its own, in wave chunks of 16 MFMA rows (16 / G tokens x
+// the G heads of the group), chunks w, w + 4, ...:
 //
 //   S^T = K_t Q^T                      (64 keys x 16 rows, 16x16x32 bf16 MFMA)
 //   m = rowmax, P = 2^(S - m), l = rowsum(P)      (token-level causal mask)
@@ -14,8 +14,8 @@
 // The gathered query rows go straight from global memory into registers in
 // the B-operand layout of S^T (lane (q, j) holds features 32kb + 8q .. +7 of
 // row j), so there is no shared query tile and no barrier after the K/V
-// load; each wave fetches its next chunk's rows while it computes the current
-// one, with the list entries read one chunk further ahead.  The S^T
+// load; each wave has its next chunk's rows in flight while it computes the
+// current one, with the list entries read one chunk further ahead.  The S^T
 // accumulator layout (lane (q, j) holds keys 4q + r of row j) is used directly
 // as the P^T operand of the second product, pairing key tiles {4q..4q+3} and
 // {16+4q..16+4q+3}; V_t^T is read with transposing LDS loads over the same
@@ -23,6 +23,17 @@
 // consecutive features of one row; a wave stages its 16 rows in LDS and
 // stores them as full 16-byte lanes, with non-temporal stores (only the merge
 // reads them, so they should not displace the rows and tiles the kernel reuses).
+//
+// What bounds it: the gathers and partials at 4 x 32k (15.1 GB in 2.20 ms,
+// 6.8 TB/s between the L2s and the memory side), and in small problems the
+// chain of one unit: record -> entries -> rows -> products -> stores, about 8 us
+// for a few chunks.  Short units (unit_size in api.hip) keep that chain the
+// longest thing that runs: with units of 2048 entries the list that every row
+// is on (block 0) took 75 us at 1k tokens and 258 us at 8k, against 16 and 113
+// us now.  Units of one block go to one XCD (xcd_item), whose L2 then loads the
+// K/V tile once: 113 against 148 us at 8k, 2.21 against 2.27 ms at 4 x 32k.
+// Splitting the lists by query rows so that a segment's rows stay in an L2 was
+// slower (2.7 ms with 4096-row segments): a tile then meets too few rows.
 //
 // Blocks of 16 or 32 tokens run on the same 64-key tiles: each list entry
 // carries the mask of the 16-key quarters its row selected, and keys of the
@@ -47,64 +58,68 @@ __global__ __launch_bounds__(256, 3) void attn_fwd_sparse_kernel(const bf16_t *_
                                                               const bf16_t *__restrict__ V, Geom gm, IndexWs ix,
                                                               bf16_t *__restrict__ opart, float2 *__restrict__ ml) {
   constexpr int TW = 16 / G;         // query tokens per wave chunk
-  constexpr int KP = D + 16;         // K pitch: 16-byte row reads of 16 rows are conflict-free at D + 16
-  constexpr int VPR = D / 8;         // 16-byte vectors per row
   constexpr int KB = D / 32;
   constexpr int NT = D / 16;
-  constexpr int SP = D + 8;          // pitch of the per-wave output staging rows
-  __shared__ __attribute__((aligned(16))) bf16_t Ks[64 * KP];
-  // V is read by transposing reads only; it is stored without padding in the
-  // swizzled layout of swz() (with D + 8 padding those reads conflict, and D + 16
-  // would not leave three workgroups per CU)
+  // K and V tiles, copied straight from global memory in the swizzled layout of swz()
+  __shared__ __attribute__((aligned(16))) bf16_t Ks[64 * D];
   __shared__ __attribute__((aligned(16))) bf16_t Vs[64 * D];
+  constexpr int SP = D + 8;          // pitch of the per-wave output staging rows
   __shared__ __attribute__((aligned(16))) bf16_t Os[4][16 * SP];  // per-wave partial rows
 
-  const int u = blockIdx.x;
-  if (u >= ix.totals[1]) return;
-  const int2 unit = ix.units[u];
-  const int bgt = unit.x, e0 = unit.y;
-  const int n_ent = min(ix.cnt[bgt] - e0, ix.unit_tokens);
-  const int bg = bgt / gm.T, t = bgt - bg * gm.T;
+  // this workgroup's unit
+  const int item = xcd_item(blockIdx.x, gridDim.x);
+  const int bg = item / ix.funits_bg, idx = item - bg * ix.funits_bg;
+  // the unit's record is read beside the count that tells whether it exists
+  const int2 unit = ix.funits[(int64_t)bg * ix.funits_bg + idx];
+  if (idx >= ix.fcnt[bg]) return;
+  const int t = unit.x >> 16, n_ent = unit.x & 0xffff;
   const int b = bg / gm.Hkv, g = bg - b * gm.Hkv;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, q4 = lane >> 4, kq = q4 * 8;
-  // list position of the unit's first entry, read once (a load inside the chunk loop
-  // would make the wait for it also wait for the prefetched rows)
-  const int64_t list0 = (int64_t)ix.off[bgt] + e0;
+  const int64_t list0 = unit.y;  // list position of the unit's first entry
   const int32_t *list = ix.tok + list0;
 
-  for (int x = tid; x < 64 * VPR; x += 256) {
-    const int kk = x / VPR, c = (x % VPR) * 8;
-    const int64_t grow = ((int64_t)b * gm.Lk + (int64_t)t * 64 + kk) * gm.Hkv + g;
-    *reinterpret_cast<uint4 *>(&Ks[kk * KP + c]) = *reinterpret_cast<const uint4 *>(K + grow * D + c);
-    *reinterpret_cast<uint4 *>(&Vs[swz<D>(kk, c)]) = *reinterpret_cast<const uint4 *>(V + grow * D + c);
-  }
-  __syncthreads();
-
-  // lane (q, j) works on row j = l16 of the wave chunk: token j / G, head j % G
+  // lane (q, j) works on row j = l16 of the wave chunk: token j / G, head j % G.
+  // Rows past the list take its last entry (their results are not stored).
   const int hh = l16 % G;
   const int nch = (n_ent + TW - 1) / TW;
-  // Loads are issued unconditionally (rows past the list read its last entry,
-  // or query row 0): their results are masked, and a fixed number of loads per
-  // chunk lets the compiler wait for exactly the ones a chunk needs.
-  auto entry = [&](int c) {
-    const int tk = c * TW + l16 / G;
-    const int v = list[min(tk, n_ent - 1)];
-    return tk < n_ent ? v : -1;
-  };
+  auto entry = [&](int c) { return list[min(c * TW + l16 / G, n_ent - 1)]; };
+  const bf16_t *qg = Q + ((int64_t)b * gm.Lq * gm.Hq + g * G + hh) * D + kq;
+  const int64_t qstep = (int64_t)gm.Hq * D;
   auto fetch = [&](int e, bf16x8 (&qf)[KB]) {
-    const int64_t row = e >= 0 ? (e >> 10) : 0;  // an empty chunk row is masked to zero weight
+    const bf16_t *src = qg + (e >> 10) * qstep;
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb)
-      qf[kb] = load_bf16x8(Q + (((int64_t)b * gm.Lq + row) * gm.Hq + g * G + hh) * D + kb * 32 + kq);
+    for (int kb = 0; kb < KB; ++kb) qf[kb] = load_bf16x8(src + kb * 32);
+    // the loads stay here, ahead of the chunk that runs while they are in
+    // flight (the scheduler would sink them into its second half)
+    __builtin_amdgcn_sched_barrier(0);
   };
+  // the first chunks' entries, then the tile copies (so that waiting for the
+  // entries leaves the copies in flight)
+  int e_a = entry(wave), e_b = entry(wave + 4), e_c = entry(wave + 8);
+  __builtin_amdgcn_sched_barrier(0);
+  {
+    const int64_t krow0 = ((int64_t)b * gm.Lk + (int64_t)t * 64) * gm.Hkv + g;
+    const int kstep = gm.Hkv * D;
+    tile_dma<D>(K + krow0 * D, [&](int r) { return r * kstep; }, Ks, wave, lane);
+    tile_dma<D>(V + krow0 * D, [&](int r) { return r * kstep; }, Vs, wave, lane);
+  }
+  bf16x8 qa[KB], qb[KB];
+  fetch(e_a, qa);
+  fetch(e_b, qb);
+  dma_wait();  // the copies (and the rows just fetched) have landed
+  lds_barrier();
 
   const float sl2 = gm.scale * kLog2e;
   const int key0 = t * 64;
-  // rows of discarded stores (past a chunk's end): one spare partial row
-  const int64_t discard = ix.discard;
+  // The unit's partials as buffers that end with it: stores of rows past the
+  // list fall outside and are dropped, without a branch, so a chunk issues a
+  // fixed number of stores and the waits for the prefetched rows need not
+  // wait for them.
+  const auto obuf = __builtin_amdgcn_make_buffer_rsrc(opart + list0 * G * D, 0, n_ent * G * D * 2, 0x00020000);
+  const auto mbuf = __builtin_amdgcn_make_buffer_rsrc(ml + list0 * G, 0, n_ent * G * 8, 0x00020000);
 
-  // one wave chunk: rows of list entry e (-1: none) with query fragments q
+  // one wave chunk: rows of list entry e with query fragments q
   auto chunk = [&](int c, int e, const bf16x8 (&q)[KB]) {
     f32x4 st[4];
 #pragma unroll
@@ -113,10 +128,10 @@ __global__ __launch_bounds__(256, 3) void attn_fwd_sparse_kernel(const bf16_t *_
     for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
       for (int kt = 0; kt < 4; ++kt)
-        st[kt] = mfma16x16x32(load_bf16x8(&Ks[(kt * 16 + l16) * KP + kb * 32 + kq]), q[kb], st[kt]);
+        st[kt] = mfma16x16x32(load_bf16x8(&Ks[swz<D>(kt * 16 + l16, kb * 32 + kq)]), q[kb], st[kt]);
     // key tile kt is quarter kt of the block: allowed if the row selected it
-    const int pos = e >= 0 ? gm.q_pos0 + (e >> 10) : -1;
-    const int qm = e >= 0 ? (e >> 6) & 15 : 0;
+    const int pos = gm.q_pos0 + (e >> 10);
+    const int qm = (e >> 6) & 15;
     float mx = -INFINITY;
 #pragma unroll
     for (int kt = 0; kt < 4; ++kt)
@@ -127,8 +142,7 @@ __global__ __launch_bounds__(256, 3) void attn_fwd_sparse_kernel(const bf16_t *_
         st[kt][r] = v;
         mx = fmaxf(mx, v);
       }
-    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    mx = max_xor32(max_xor16(mx));
     if (mx == -INFINITY) mx = 0.f;
     float l = 0.f;
 #pragma unroll
@@ -152,12 +166,9 @@ __global__ __launch_bounds__(256, 3) void attn_fwd_sparse_kernel(const bf16_t *_
       ot[nt] = mfma16x16x32(lds_col8_sw<D>(Vs, 32 + q4 * 4, 48 + q4 * 4, nt * 16, l16), pb1, ot[nt]);
     }
     // The chunk's 16 partial rows are one contiguous run of the list-ordered
-    // partial buffer (entries c*TW.., heads inner): stage them in LDS and write
-    // full 16-byte lanes.  Every lane stores (unused lanes to the discard row),
-    // so a chunk issues a fixed number of stores and the waits for the
-    // prefetched rows need not wait for them.
-    const int64_t run0 = list0 + c * TW;  // list position of the chunk's first entry
-    st_stream_f2(&ml[e >= 0 && q4 == 0 ? (run0 + l16 / G) * G + hh : discard], mx, l);
+    // partial buffer: staged in LDS and stored as whole rows (16-byte pieces in
+    // the accumulator layout, 64 bytes of a row per store, took 3.2 ms at 4 x
+    // 32k against 2.2, 175 us at 8k against 118).
     bf16_t *os = Os[wave];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
@@ -166,31 +177,30 @@ __global__ __launch_bounds__(256, 3) void attn_fwd_sparse_kernel(const bf16_t *_
       *reinterpret_cast<uint2 *>(&os[l16 * SP + nt * 16 + q4 * 4]) = *reinterpret_cast<const uint2 *>(o4);
     }
     wave_lds_sync();
-    const int nrows = min(TW, n_ent - c * TW) * G;  // valid rows of this chunk
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, f32x2{mx, l}), mbuf,
+                                          q4 == 0 ? (c * 16 + l16) * 8 : 0x7fffffff, 0, 2);
 #pragma unroll
     for (int k = 0; k < 16 * D / 8 / 64; ++k) {
       const int v = lane + 64 * k, r = v / (D / 8), cc = (v % (D / 8)) * 8;
-      const int64_t row = r < nrows ? run0 * G + r : discard;
-      st_stream16(opart + row * D + cc, &os[r * SP + cc]);
+      __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4 *>(&os[r * SP + cc]), obuf,
+                                             ((c * 16 + r) * D + cc) * 2, 0, 2);
     }
     wave_lds_sync();
   };
 
-  // Two register sets alternate: while one chunk computes, the next one's rows
-  // are in flight in the other set and the entries of the one after that too.
-  int e_a = entry(wave), e_b = entry(wave + 4);
-  bf16x8 qa[KB], qb[KB];
-  fetch(e_a, qa);
+  // Two register sets take turns: a set is refilled as soon as its chunk is
+  // done, so the next chunk's rows and the entries of the one after are always
+  // in flight.
   for (int c = wave; c < nch; c += 8) {
-    int e_n = entry(c + 8);
-    fetch(e_b, qb);
     chunk(c, e_a, qa);
     if (c + 4 >= nch) break;
-    e_a = e_n;
-    e_n = entry(c + 12);
+    e_a = e_c;
     fetch(e_a, qa);
+    e_c = entry(c + 12);
     chunk(c + 4, e_b, qb);
-    e_b = e_n;
+    e_b = e_c;
+    fetch(e_b, qb);
+    e_c = entry(c + 16);
   }
 }
 
@@ -262,7 +272,7 @@ template <int D, int G>
 static hipError_t launch_fwd_t(const Geom &g, const void *Q, const void *K, const void *V, void *O, float *LSE,
                                const IndexWs &ix, void *opart, float2 *ml, hipStream_t s) {
   timing_begin("phsa_attn_fwd_sparse", s);
-  hipLaunchKernelGGL((attn_fwd_sparse_kernel<D, G>), dim3((unsigned)ix.units_max), dim3(256), 0, s,
+  hipLaunchKernelGGL((attn_fwd_sparse_kernel<D, G>), dim3((unsigned)(g.B * g.Hkv * ix.funits_bg)), dim3(256), 0, s,
                      static_cast<const bf16_t *>(Q), static_cast<const bf16_t *>(K), static_cast<const bf16_t *>(V),
                      g, ix, static_cast<bf16_t *>(opart), ml);
   timing_end(s);

@@ -13,6 +13,7 @@ typedef uint16_t bf16_t;  // storage type of bfloat16 values
 // 16 raw bytes as a native vector: loads and stores of it are single values
 // (a uint4 struct copy can be lowered to a memcpy through scratch memory)
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kWave = 64;
 constexpr float kLog2e = 1.4426950408889634f;

@@ -22,10 +22,8 @@
 // Integer-only passes, all deterministic (no order depends on timing):
 //   count : per 256-row tile, an LDS bitmap [8 words][T] of who selected
 //           what; popcounts give per-tile counts cntw[bg][w][t].
-//   scan1 : per (bg, t), exclusive prefix over tiles -> cntw, total -> cnt,
-//           and per 256 (bg, t) the sums of list lengths and units.
-//   scan2 : one workgroup turns those sums into offsets; then per (bg, t)
-//           the list offsets, unit offsets and the unit table.
+//   scan  : one workgroup per bg: per t the exclusive prefix over tiles -> toff
+//           and the total -> cnt; over t the list and unit offsets and the unit tables.
 //   fill  : rebuilds the tile bitmap; an entry's place in its list is
 //           tile offset + number of lower rows in the tile that chose t.
 #include "common.h"
@@ -225,125 +223,128 @@ __global__ __launch_bounds__(256) void index_count_kernel(const int32_t *__restr
   }
 }
 
-// The list scans.  For x = (b, g, t) with list length c: nu = ceil(c /
-// unit_tokens) work units, and the flag f = (nu != 1) of the blocks whose
-// dK/dV the finalize writes (from partial sums, or zeros for an empty list).
-// Exclusive prefixes over x of c, nu and f give the list offsets, the unit
-// offsets and the places in the finalize list.  Three passes, each x one
-// thread: per 256 x the sums (with the tile scan), one workgroup's scan of
-// those sums, then per 256 x the offsets and the unit table.
-struct Counts3 {
-  int c, nu, f;
+// The scans over t.  For a list of c entries: nu = ceil(c / unit_tokens)
+// backward units, the flag f = (nu != 1) of the blocks whose dK/dV the
+// finalize writes (from partial sums, or zeros for an empty list), and nf
+// forward units.
+struct ListCounts {
+  int c, nu, f, nf;
+  __device__ __forceinline__ void add(const ListCounts &o) {
+    c += o.c;
+    nu += o.nu;
+    f += o.f;
+    nf += o.nf;
+  }
 };
 
-__device__ __forceinline__ Counts3 list_counts(int c, int unit_tokens, bool live) {
-  const int nu = (c + unit_tokens - 1) / unit_tokens;
-  return Counts3{c, nu, live && nu != 1 ? 1 : 0};
-}
+constexpr int kScanThreads = 512;
 
-// Exclusive scan of v over a 256-thread workgroup (c, nu and f each on its
-// own); tot receives the workgroup's sums.  Holds barriers.
-__device__ __forceinline__ Counts3 block_scan3(Counts3 v, Counts3 &tot) {
-  __shared__ Counts3 wsum_s[4];
+// Exclusive scan of v over the workgroup (each field on its own); tot receives
+// the workgroup's sums.  Holds barriers.
+__device__ __forceinline__ ListCounts block_scan(ListCounts v, ListCounts &tot) {
+  constexpr int NW = kScanThreads / 64;
+  __shared__ ListCounts wsum_s[NW];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  Counts3 inc = v;
+  ListCounts inc = v;
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
-    const int a = __shfl_up(inc.c, d, 64), b = __shfl_up(inc.nu, d, 64), f = __shfl_up(inc.f, d, 64);
-    if (lane >= d) {
-      inc.c += a;
-      inc.nu += b;
-      inc.f += f;
-    }
+    const ListCounts o{__shfl_up(inc.c, d, 64), __shfl_up(inc.nu, d, 64), __shfl_up(inc.f, d, 64),
+                       __shfl_up(inc.nf, d, 64)};
+    if (lane >= d) inc.add(o);
   }
   if (lane == 63) wsum_s[wave] = inc;
   __syncthreads();
-  Counts3 pre{0, 0, 0};
-  tot = Counts3{0, 0, 0};
+  ListCounts pre{0, 0, 0, 0};
+  tot = ListCounts{0, 0, 0, 0};
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    const Counts3 s = wsum_s[w];
-    if (w < wave) {
-      pre.c += s.c;
-      pre.nu += s.nu;
-      pre.f += s.f;
-    }
-    tot.c += s.c;
-    tot.nu += s.nu;
-    tot.f += s.f;
+  for (int w = 0; w < NW; ++w) {
+    const ListCounts s = wsum_s[w];
+    if (w < wave) pre.add(s);
+    tot.add(s);
   }
   __syncthreads();  // wsum_s may be reused by the caller's next scan
-  return Counts3{pre.c + inc.c - v.c, pre.nu + inc.nu - v.nu, pre.f + inc.f - v.f};
+  return ListCounts{pre.c + inc.c - v.c, pre.nu + inc.nu - v.nu, pre.f + inc.f - v.f, pre.nf + inc.nf - v.nf};
 }
 
-// Per (b, g, t): the tile counts become tile offsets (exclusive over the
-// query tiles) and their total the list length; then the workgroup's sums.
-__global__ __launch_bounds__(256) void index_scan_tiles_kernel(Geom gm, IndexWs ix, int nbgt) {
-  const int x = blockIdx.x * 256 + threadIdx.x;
-  const bool live = x < nbgt;
-  int run = 0;
-  if (live) {
-    const int bg = x / gm.T, t = x % gm.T;
-    int32_t *col = ix.cntw + (int64_t)bg * ix.W * gm.T + t;
-    // a batch of tiles' counts is loaded before any of them is overwritten (a
-    // load behind a store waits for the store too: one round trip per batch)
-    constexpr int U = 32;
-    for (int w0 = 0; w0 < ix.W; w0 += U) {
+// One workgroup per bg: per t the exclusive prefix of the tile counts (toff),
+// then over t the list offsets, the unit tables and the finalize list.  Every
+// bg keeps its lists and units in regions of its own, so no prefix crosses
+// workgroups and one launch does it.  tp (a power of two) threads cover the
+// blocks; with few blocks the kScanThreads / tp thread groups share the tiles.
+__global__ __launch_bounds__(kScanThreads) void index_scan_kernel(Geom gm, IndexWs ix, int tp) {
+  __shared__ int part_s[kScanThreads];
+  const int bg = blockIdx.x, tid = threadIdx.x;
+  const int32_t *cw = ix.cntw + (int64_t)bg * ix.W * gm.T;
+  int32_t *to = ix.toff + (int64_t)bg * ix.W * gm.T;
+  int2 *fu = ix.funits + (int64_t)bg * ix.funits_bg;
+  int4 *un = ix.units + (int64_t)bg * ix.units_bg;
+  const int ng = kScanThreads / tp, grp = tid / tp;  // tile groups, this thread's
+  const int wper = (ix.W + ng - 1) / ng, w0 = min(grp * wper, ix.W), w1 = min(w0 + wper, ix.W);
+  ListCounts carry{(int)((int64_t)bg * gm.Lq * (gm.ksel - gm.band)), 0, 0, 0};  // first list position of this bg
+  constexpr int U = 32;
+  for (int t0 = 0; t0 < gm.T; t0 += tp) {
+    const int t = t0 + tid % tp;
+    const int tc = min(t, gm.T - 1);
+    // counts of the group's tiles; a batch is loaded before its prefixes are
+    // stored (a load behind a store waits for the store too)
+    int run = 0;
+    if (ng > 1) {
+      for (int w = w0; w < w1; w += U) {
+        int c[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) c[u] = cw[(int64_t)min(w + u, w1 - 1) * gm.T + tc];
+#pragma unroll
+        for (int u = 0; u < U; ++u) run += w + u < w1 ? c[u] : 0;
+      }
+      __syncthreads();
+      part_s[tid] = run;
+      __syncthreads();
+      run = 0;
+      for (int x = 0; x < grp; ++x) run += part_s[x * tp + tid % tp];
+    }
+    for (int w = w0; w < w1; w += U) {
       int c[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) c[u] = w0 + u < ix.W ? col[(int64_t)(w0 + u) * gm.T] : 0;
+      for (int u = 0; u < U; ++u) c[u] = cw[(int64_t)min(w + u, w1 - 1) * gm.T + tc];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (w0 + u < ix.W) col[(int64_t)(w0 + u) * gm.T] = run;
-        run += c[u];
-      }
+      for (int u = 0; u < U; ++u)
+        if (w + u < w1) {
+          if (t < gm.T) to[(int64_t)(w + u) * gm.T + t] = run;
+          run += c[u];
+        }
     }
-    ix.cnt[x] = run;
+    // list lengths: the last group's running sums, taken by the first tp threads
+    if (ng > 1) {
+      __syncthreads();
+      if (grp == ng - 1) part_s[tid % tp] = run;
+      __syncthreads();
+      run = part_s[tid % tp];
+    }
+    const bool live = grp == 0 && t < gm.T;
+    if (!live) run = 0;
+    const int nu = (run + ix.unit_tokens - 1) / ix.unit_tokens, nf = (run + ix.fpart - 1) / ix.fpart;
+    const ListCounts v{run, nu, live && nu != 1 ? 1 : 0, nf};
+    ListCounts tot, at = block_scan(v, tot);
+    at.add(carry);
+    if (live) {
+      const int x = bg * gm.T + t;
+      ix.off[x] = at.c;
+      ix.uoff[(int64_t)bg * (gm.T + 1) + t] = at.nu;
+      for (int u = 0; u < nu; ++u)
+        un[at.nu + u] =
+            make_int4(x, min(ix.unit_tokens, run - u * ix.unit_tokens), at.c + u * ix.unit_tokens, nu == 1 ? 1 : 0);
+      if (v.f) ix.fin[(int64_t)bg * gm.T + at.f] = x;
+      for (int u = 0; u < nf; ++u)
+        fu[at.nf + u] = make_int2((t << 16) | min(ix.fpart, run - u * ix.fpart), at.c + u * ix.fpart);
+    }
+    carry.add(tot);
   }
-  Counts3 tot;
-  block_scan3(list_counts(run, ix.unit_tokens, live), tot);
-  if (threadIdx.x == 0) ix.wsum[blockIdx.x] = make_int4(tot.c, tot.nu, tot.f, 0);
-}
-
-// One workgroup: the workgroup sums become exclusive offsets (in place), and
-// the totals (entries, units, finalize blocks) are written.
-__global__ __launch_bounds__(256) void index_scan_sums_kernel(IndexWs ix, int nw, int nbgt) {
-  Counts3 carry{0, 0, 0};
-  for (int b0 = 0; b0 < nw; b0 += 256) {
-    const int j = b0 + (int)threadIdx.x;
-    const int4 v = j < nw ? ix.wsum[j] : make_int4(0, 0, 0, 0);
-    Counts3 tot;
-    const Counts3 ex = block_scan3(Counts3{v.x, v.y, v.z}, tot);
-    if (j < nw) ix.wsum[j] = make_int4(carry.c + ex.c, carry.nu + ex.nu, carry.f + ex.f, 0);
-    carry.c += tot.c;
-    carry.nu += tot.nu;
-    carry.f += tot.f;
+  if (tid == 0) {
+    ix.uoff[(int64_t)bg * (gm.T + 1) + gm.T] = carry.nu;
+    ix.ucnt[bg] = carry.nu;
+    ix.nfin[bg] = carry.f;
+    ix.fcnt[bg] = carry.nf;
   }
-  if (threadIdx.x == 0) {
-    ix.off[nbgt] = carry.c;
-    ix.uoff[nbgt] = carry.nu;
-    ix.totals[0] = carry.c;
-    ix.totals[1] = carry.nu;
-    ix.totals[2] = carry.f;
-  }
-}
-
-// Per x: list offset, first unit, the unit table entries (block, first list
-// entry) and, for nu != 1, the place in the finalize list (ascending x).
-__global__ __launch_bounds__(256) void index_write_lists_kernel(IndexWs ix, int nbgt) {
-  const int x = blockIdx.x * 256 + threadIdx.x;
-  const bool live = x < nbgt;
-  const int c = live ? ix.cnt[x] : 0;
-  const int4 base = ix.wsum[blockIdx.x];
-  Counts3 tot;
-  const Counts3 v = list_counts(c, ix.unit_tokens, live);
-  const Counts3 ex = block_scan3(v, tot);
-  if (!live) return;
-  const int rb = base.y + ex.nu;
-  ix.off[x] = base.x + ex.c;
-  ix.uoff[x] = rb;
-  for (int u = 0; u < v.nu; ++u) ix.units[rb + u] = make_int2(x, u * ix.unit_tokens);
-  if (v.f) ix.fin[base.z + ex.f] = x;
 }
 
 // Writes each row's entries into their lists, its position-map row (list
@@ -365,7 +366,7 @@ __global__ __launch_bounds__(256) void index_fill_kernel(const int32_t *__restri
   const int logical = xcd_item(blockIdx.x + blockIdx.y * gridDim.x, gridDim.x * gridDim.y);
   const int w = logical % gridDim.x, bg = logical / gridDim.x, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int32_t *tile_off = ix.cntw + ((int64_t)bg * ix.W + w) * gm.T;
+  const int32_t *tile_off = ix.toff + ((int64_t)bg * ix.W + w) * gm.T;
   const int32_t *list_off = ix.off + (int64_t)bg * gm.T;
   for (int t = tid; t < gm.T; t += 256) base_s[t] = list_off[t] + tile_off[t];
   build_tile_bitmap(bm, rows_s, sel, gm, bg, w);  // its barriers also publish base_s
@@ -464,23 +465,17 @@ hipError_t launch_build_index(const Geom &g, const int32_t *sel, const IndexWs &
   // Each launch's status is taken right after it: the attention kernels gather
   // through these lists, so a failed pass must stop the chain before them.
   hipError_t e;
-  const int nbgt = g.B * g.Hkv * g.T;
   const size_t lds = index_lds_bytes(g);
   timing_begin("phsa_index_count", s);
   hipLaunchKernelGGL(index_count_kernel, dim3(ix.W, g.B * g.Hkv), dim3(256), lds, s, sel, g, ix);
   timing_end(s);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  const int nw = (nbgt + 255) / 256;  // list-scan workgroups (ix.wsum entries)
-  timing_begin("phsa_index_scan_tiles", s);
-  hipLaunchKernelGGL(index_scan_tiles_kernel, dim3(nw), dim3(256), 0, s, g, ix, nbgt);
+  timing_begin("phsa_index_scan", s);
+  int tp = 64;
+  while (tp < g.T && tp < kScanThreads) tp *= 2;
+  hipLaunchKernelGGL(index_scan_kernel, dim3(g.B * g.Hkv), dim3(kScanThreads), 0, s, g, ix, tp);
   timing_end(s);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  timing_begin("phsa_index_scan_lists", s);
-  hipLaunchKernelGGL(index_scan_sums_kernel, dim3(1), dim3(256), 0, s, ix, nw, nbgt);
-  if ((e = hipGetLastError()) == hipSuccess)
-    hipLaunchKernelGGL(index_write_lists_kernel, dim3(nw), dim3(256), 0, s, ix, nbgt);
-  timing_end(s);
-  if (e != hipSuccess || (e = hipGetLastError()) != hipSuccess) return e;
   timing_begin("phsa_index_fill", s);
   hipLaunchKernelGGL(index_fill_kernel, dim3(ix.W, g.B * g.Hkv), dim3(256),
                      lds + (size_t)g.T * (sizeof(int32_t) + sizeof(uint64_t)), s, sel,

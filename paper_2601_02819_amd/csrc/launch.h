@@ -24,25 +24,30 @@ struct Geom {
 };
 
 // Index (inverted selection) workspace, carved out of the caller's buffer.
+// R = B * Hkv.  Every (b, g) has regions of its own (lists, work units, forward
+// units), so no pass needs a prefix over all of them.
 struct IndexWs {
   int W;              // query tiles of kIndexTile rows
-  int unit_tokens;    // list entries per attention work unit
-  int64_t units_max;  // upper bound on the number of work units
+  int unit_tokens;    // list entries per backward work unit
+  int units_bg;       // backward units reserved per (b, g)
+  int fpart;          // list entries per forward unit
+  int funits_bg;      // forward units reserved per (b, g)
   int64_t nnz_max;    // upper bound on list entries
-  int32_t *cntw;      // [B*Hkv, W, T]  per-tile counts, then per-tile list offsets
-  int32_t *cnt;       // [B*Hkv*T]      list length per (b, g, t)
-  int32_t *off;       // [B*Hkv*T + 1]  list start per (b, g, t)
-  int32_t *uoff;      // [B*Hkv*T + 1]  first work unit per (b, g, t)
-  int32_t *totals;    // [4]            nnz, n_units, blocks in fin
-  int4 *wsum;         // [ceil(B*Hkv*T / 256)] per 256 (b, g, t): sums of list lengths, units and
-                      //                 finalize flags, then their exclusive offsets
-  int32_t *fin;       // [B*Hkv*T]      the (b, g, t) whose dK/dV the finalize writes (not one work unit)
+  int32_t *cntw;      // [R, W, T]      per-tile counts
+  int32_t *toff;      // [R, W, T]      exclusive prefix of cntw over the tiles
+  int32_t *cnt;       // [R * T]        list length per (b, g, t)
+  int32_t *off;       // [R * T]        list start per (b, g, t)
+  int32_t *uoff;      // [R, T + 1]     first backward unit of (b, g, t) within its (b, g)'s
+  int32_t *ucnt;      // [R]            backward units of (b, g)
+  int32_t *nfin;      // [R]            blocks of (b, g) in fin
+  int32_t *fin;       // [R, T]         the (b, g, t) whose dK/dV the finalize writes (not one work unit)
+  int32_t *fcnt;      // [R]            forward units of (b, g)
   int32_t *tok;       // [nnz_max]      (query row << 10) | (quarter mask << 6) | slot, ascending row per list
   int32_t *pmap;      // [B*Hkv*Lq*Ksel] list position of each valid (row, slot); partials are
                       //                 stored in list order and the merges gather through this map
-  int2 *units;        // [units_max]    (b*Hkv*T + g*T + t, first list entry)
+  int4 *units;        // [R, units_bg]  (b*Hkv*T + g*T + t, entries, list position of the first, 1: the whole list)
+  int2 *funits;       // [R, funits_bg] ((t << 16) | entries, list position of the first)
   int64_t band_base;  // list position of the band partial of row (b, g, i): band_base + (b*Hkv + g)*Lq + i
-  int64_t discard;    // partial row that absorbs stores past a chunk's end (after the list and band rows)
   uint8_t *bflag;     // [B*Hkv*Lq] 1: the row's forced blocks are in the band (NULL: no band)
 };
 
