@@ -157,27 +157,22 @@ size_t fwd_layout(const Geom &g0, char *base, FwdWs *ws) {
 }
 
 size_t bwd_layout(const Geom &g0, char *base, BwdWs *ws) {
+  if (g0.dtype == PHSA_FP32) return fp32_bwd_layout(g0, base, nullptr);
   BwdWs w{};
-  w.co = Coarse{tile_geom(g0), nullptr};
+  size_t off = coarse_layout(g0, base, &w.co);
   const Geom g = w.co.gc;
-  size_t off = 0;
-  if (g.dtype == PHSA_BF16) {
-    off = coarse_layout(g0, base, &w.co);
-    off += index_layout(g, base ? base + off : nullptr, &w.ix);
-    w.ix.bflag = w.co.bflag;
-  }
+  off += index_layout(g, base ? base + off : nullptr, &w.ix);
+  w.ix.bflag = w.co.bflag;
   w.Dvec = base ? reinterpret_cast<float *>(base + off) : nullptr;
   off += align_up(sizeof(float) * (size_t)g.B * g.Hq * g.Lq);
-  if (g.dtype == PHSA_BF16) {
-    const int64_t slots = w.ix.nnz_max * g.G;
-    w.dqpart = base ? base + off : nullptr;
-    off += align_up(slots * g.d * elem_bytes(g));
-    w.dkvpart = base ? reinterpret_cast<float *>(base + off) : nullptr;
-    off += align_up(sizeof(float) * (size_t)g.B * g.Hkv * w.ix.units_bg * 2 * 64 * g.d);
-    if (g.band) {
-      w.bkv = base ? reinterpret_cast<float *>(base + off) : nullptr;
-      off += align_up(sizeof(float) * (size_t)g.B * g.Hkv * g.T * 2 * 64 * g.d);
-    }
+  const int64_t slots = w.ix.nnz_max * g.G;
+  w.dqpart = base ? base + off : nullptr;
+  off += align_up(slots * g.d * elem_bytes(g));
+  w.dkvpart = base ? reinterpret_cast<float *>(base + off) : nullptr;
+  off += align_up(sizeof(float) * (size_t)g.B * g.Hkv * w.ix.units_bg * 2 * 64 * g.d);
+  if (g.band) {
+    w.bkv = base ? reinterpret_cast<float *>(base + off) : nullptr;
+    off += align_up(sizeof(float) * (size_t)g.B * g.Hkv * g.T * 2 * 64 * g.d);
   }
   if (ws) *ws = w;
   return off;
@@ -186,6 +181,17 @@ size_t bwd_layout(const Geom &g0, char *base, BwdWs *ws) {
 size_t decode_layout(const Geom &) { return 0; }  // the decode kernels need no scratch
 
 }  // namespace
+
+size_t fp32_bwd_layout(const Geom &g, char *base, Fp32BwdWs *ws) {
+  Fp32BwdWs w{};
+  w.Dvec = reinterpret_cast<float *>(base);
+  size_t off = align_up(sizeof(float) * (size_t)g.B * g.Hq * g.Lq);
+  off += index_layout(g, base ? base + off : nullptr, &w.ix);
+  w.part = base ? reinterpret_cast<float *>(base + off) : nullptr;
+  off += align_up(sizeof(float) * (size_t)g.B * g.Hkv * w.ix.units_bg * 2 * g.m * g.d);
+  if (ws) *ws = w;
+  return off;
+}
 
 // bf16 selection scratch, as launch_select carves it: K_comp split into bf16 hi
 // and lo [B, Hkv, T, d] each, then the norms of both parts per block (float2).
@@ -417,13 +423,13 @@ phsa_status phsa_attn_bwd(const phsa_params *p, const void *Q, const void *K, co
     if (!Q || !K || !V || !O || !dO || !LSE || !sel || !dQ || !dK || !dV) return PHSA_ERR_NULL;
     if ((st = check_ws(g, PHSA_OP_ATTN_BWD, ws, ws_bytes)) != PHSA_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    BwdWs w;
-    bwd_layout(g, static_cast<char *>(ws), &w);
     if (g.dtype == PHSA_FP32)
       return from_hip(launch_attn_bwd_fp32(g, static_cast<const float *>(Q), static_cast<const float *>(K),
                                            static_cast<const float *>(V), static_cast<const float *>(O),
                                            static_cast<const float *>(dO), LSE, sel, static_cast<float *>(dQ),
-                                           static_cast<float *>(dK), static_cast<float *>(dV), w.Dvec, s));
+                                           static_cast<float *>(dK), static_cast<float *>(dV), static_cast<float *>(ws), s));
+    BwdWs w;
+    bwd_layout(g, static_cast<char *>(ws), &w);
     const bool reuse = (p->flags & PHSA_FLAG_REUSE_INDEX) != 0;
     return from_hip(launch_attn_bwd(w.co.gc, Q, K, V, O, dO, LSE, sel, dQ, dK, dV, w.ix, w.Dvec, w.dqpart, w.dkvpart,
                                     w.bkv, reuse, s));

@@ -99,7 +99,14 @@ hipError_t launch_attn_fwd_fp32(const Geom &g, const float *Q, const float *K, c
                                 const int32_t *sel, float *O, float *LSE, hipStream_t s);
 hipError_t launch_attn_bwd_fp32(const Geom &g, const float *Q, const float *K, const float *V,
                                 const float *O, const float *dO, const float *LSE, const int32_t *sel,
-                                float *dQ, float *dK, float *dV, float *Dvec, hipStream_t s);
+                                float *dQ, float *dK, float *dV, float *ws, hipStream_t s);
+// The float32 backward's workspace (laid out in api.hip; base NULL: size only).
+struct Fp32BwdWs {
+  float *Dvec;   // [B, Lq, Hq] rowsum(dO * O)
+  IndexWs ix;    // the lists of the selection's own blocks
+  float *part;   // [R * units_bg][2][m][d] dK, dV sums of units that hold part of a list
+};
+size_t fp32_bwd_layout(const Geom &g, char *base, Fp32BwdWs *ws);
 hipError_t launch_decode(const Geom &g, const void *Q, const void *K, const void *V, const float *Kc,
                          const int32_t *clen, int32_t *sel, void *O, float *LSE, hipStream_t s);
 hipError_t launch_cache_append(const Geom &g, const void *Kn, const void *Vn, const uint8_t *pn, void *Kcache,
