@@ -1,18 +1,28 @@
 // One decode step with a block KV cache: each of B sequences has one new
 // query at position Lk - 1 (its key/value are already in the cache), scores
 // the cache's T block representatives, selects, and attends over the chosen
-// blocks (Eq. 8, Algorithm 1 selection, Eq. 10-11).  All three kernels are
-// memory-bound: the representatives and the selected K/V blocks are each
-// read once.
+// blocks (Eq. 8, Algorithm 1 selection, Eq. 10-11): one kernel, one workgroup
+// per (b, g).
 //
-//   decode_select : one workgroup of 8 waves per (b, g).  Lanes read K_comp
-//                   rows as float4 (D / 4 lanes per row, 8 loads in flight
-//                   each) and reduce a row's dot product by shuffles; the
-//                   top-k (score desc, block asc) comes from per-wave bitonic
-//                   sorts of 64-candidate chunks merged pairwise in LDS.
-//   decode_attn   : one workgroup per (b, g) streams its selected K/V blocks
-//                   with coalesced 16-byte loads, keeps a running softmax per
-//                   wave and merges the waves in LDS: O and LSE directly.
+//   scores : lanes read K_comp rows as float4 (D / 4 lanes per row, U loads in
+//            flight each) and reduce a row's dot product with DPP moves; the
+//            scores stay in LDS.
+//   top-k  : one wave holds all scores in registers and takes the best one
+//            (score desc, block asc) top_k times, a wave maximum each; then it
+//            writes the sel row and leaves the slot list in LDS.
+//   attend : the selected keys, slot after slot, are dealt to the waves in
+//            groups of KG keys with NI 16-byte loads of K and of V in flight per
+//            lane; a running softmax per wave, merged in LDS into O and LSE.
+//
+// Both reads are bound by HBM when there are sequences enough to fill the chip
+// (64 x 32k: 370 MB in 60 us, 6.2 TB/s; 75 us as a selection and an attention
+// kernel) and by what one CU can have in flight when there are few (1 x 8k:
+// about 18 bytes a cycle; 27 -> 17 us).  Up to 256 workgroups take 16 waves (one
+// per CU), more of them 8, so that two share a CU and one's top-k runs beside
+// the other's loads (64 x 32k with 16 waves: 88 against 81 us in the vector
+// version).  Long caches of few sequences score in slices (decode_scan_kernel; 6 x
+// 32k in 2048 blocks: 70 us with two kernels, 32 with one, 28 in slices).
+//
 // With per-sequence cache lengths (phsa_decode_varlen) sequence b's query sits
 // at position len[b] - 1; its own block may be partly written, and keys past
 // the query are masked without reading their values.  cache_append adds one
@@ -20,52 +30,13 @@
 #include <float.h>
 #include <math.h>
 
+#include <algorithm>
+
 #include "common.h"
 #include "launch.h"
 
 namespace phsa {
 
-__device__ __forceinline__ bool beats_d(float s1, int t1, float s2, int t2) {
-  return s1 > s2 || (s1 == s2 && t1 < t2);
-}
-
-// One (score, block) pair per lane, sorted across the wave best first
-// (higher score, then lower block) by a bitonic network over shuffles.
-__device__ __forceinline__ void wave_sort_best_first(float &s, int &t, int lane) {
-#pragma unroll
-  for (int size = 2; size <= 64; size <<= 1)
-#pragma unroll
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      const float os = __shfl_xor(s, stride, 64);
-      const int ot = __shfl_xor(t, stride, 64);
-      const bool want_better = ((lane & size) == 0) == ((lane & stride) == 0);
-      if (beats_d(os, ot, s, t) == want_better && !(os == s && ot == t)) {
-        s = os;
-        t = ot;
-      }
-    }
-}
-
-// r := the best 64 of r and v, best first (both best-first sorted across the wave).
-__device__ __forceinline__ void wave_merge_best_first(float &rs, int &rt, float vs, int vt, int lane) {
-  const float ws = __shfl(vs, 63 - lane, 64);
-  const int wt = __shfl(vt, 63 - lane, 64);
-  if (beats_d(ws, wt, rs, rt)) {
-    rs = ws;
-    rt = wt;
-  }
-  // r is now bitonic; finish with the merge stages of a best-first sort
-#pragma unroll
-  for (int stride = 32; stride > 0; stride >>= 1) {
-    const float os = __shfl_xor(rs, stride, 64);
-    const int ot = __shfl_xor(rt, stride, 64);
-    const bool want_better = (lane & stride) == 0;
-    if (beats_d(os, ot, rs, rt) == want_better && !(os == rs && ot == rt)) {
-      rs = os;
-      rt = ot;
-    }
-  }
-}
 
 // Cache length of sequence b: clen[b] clamped to [1, capacity], or the
 // uniform Lk when no length array is given.
@@ -94,328 +65,599 @@ __device__ __forceinline__ float key_row_sum(float a) {
   return a;
 }
 
-// MODE 0 ranks on the summed logits of the group's heads.  MODE 1
-// (PHSA_FLAG_SELECT_SOFTMAX_SUM) keeps every head's log2 logits of the
-// complete blocks 0..cur-1 in LDS, reduces each head's log2 normaliser over
-// the workgroup, and scores a candidate by log2 sum_h 2^(x_h - lse_h).
-template <typename T, int D, int MODE>
-__global__ __launch_bounds__(512) void decode_select_kernel(const T *__restrict__ Q, const float *__restrict__ Kc,
-                                                            const int32_t *__restrict__ clen,
-                                                            int32_t *__restrict__ sel, Geom gm) {
+// Largest value over the wave, every lane getting it (DPP moves within the
+// 16-lane rows, row swaps between them).
+__device__ __forceinline__ float wave_max_dpp(float v) {
+  v = fmaxf(v, dpp_move<0xB1>(v));   // quad_perm [1, 0, 3, 2]
+  v = fmaxf(v, dpp_move<0x4E>(v));   // quad_perm [2, 3, 0, 1]
+  v = fmaxf(v, dpp_move<0x141>(v));  // row_half_mirror
+  v = fmaxf(v, dpp_move<0x140>(v));  // row_mirror
+  return max_xor32(max_xor16(v));
+}
+
+__device__ __forceinline__ float wave_min_dpp(float v) { return -wave_max_dpp(-v); }
+
+// The k best of the nc candidates sc[0 .. nc) (score desc, index asc), by one
+// wave, one pick after the other: lane l holds candidates l, l + 64, ..., and
+// each round takes the wave's maximum (the lowest index among equals) out of
+// its lane.  Lane p < k returns the p-th pick in index order; nc <= 64 PER.
+template <int PER>
+__device__ __noinline__ int wave_extract_k(const float *sc, int nc, int k) {
+  const int lane = threadIdx.x & 63;
+  float v[PER];
+  uint32_t taken = 0;  // bit j: candidate j of this lane is out (a score may be -inf itself)
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    v[j] = j * 64 + lane < nc ? sc[j * 64 + lane] : -INFINITY;
+    taken |= j * 64 + lane < nc ? 0u : 1u << j;
+  }
+  int mine = 0x7fffffff;
+  for (int p = 0; p < k; ++p) {
+    // this lane's best remaining candidate (the lowest j among equals)
+    float best = -INFINITY;
+    int bj = -1;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      const bool in = !((taken >> j) & 1) && (bj < 0 || v[j] > best);
+      best = in ? v[j] : best;
+      bj = in ? j : bj;
+    }
+    const float top = wave_max_dpp(best);
+    uint64_t m = __ballot(bj >= 0 && best == top);
+    if (m == 0) m = __ballot(bj >= 0);  // scores that compare with nothing (NaN): any remaining one
+    int low = 0x7fffffff;               // the lowest index among the equals
+    for (uint64_t x = m; x; x &= x - 1) {
+      const int l = __builtin_ctzll(x);
+      low = min(low, __builtin_amdgcn_readlane(bj, l) * 64 + l);
+    }
+    if (lane == p) mine = low;
+    if (lane == (low & 63)) taken |= 1u << (low >> 6);
+  }
+  int rank = 0;  // picks below this lane's
+  for (int j = 0; j < k; ++j) rank += __builtin_amdgcn_readlane(mine, j) < mine;
+  return __builtin_amdgcn_ds_permute((lane < k ? rank : lane) << 2, mine);
+}
+
+// The k best of the n <= 64 entries list[0 .. n) (score, index), which stand in
+// index order, so that an equal score ranks higher the earlier it stands; an
+// index below 0 marks no entry.  Lane p returns the index of the p-th of them in
+// index order (0x7fffffff past the last) and its score.
+__device__ __forceinline__ int wave_rank_k(float2 *list, int n, int k, int lane, float &score) {
+  const float2 me = lane < n ? list[lane] : make_float2(0.f, __int_as_float(-1));
+  const bool have = __float_as_int(me.y) >= 0;
+  // the score's bits in unsigned order (-0 as +0), 0 for no entry: below -inf
+  const uint32_t fb = __float_as_uint(me.x + 0.f);
+  const uint32_t key = have ? ((fb & 0x80000000u) ? ~fb : (fb | 0x80000000u)) : 0u;
+  int rank = 0;
+  for (int l0 = 0; l0 < n; l0 += 8)  // lanes past n hold no entry
+#pragma unroll
+    for (int l = l0; l < l0 + 8; ++l) rank += __builtin_amdgcn_readlane(key, l) > key;
+  uint64_t m = __ballot(have && rank < k);
+  if (__popcll(m) > k) {  // equal scores across the k-th place: the earlier ones
+    for (int l = 0; l < n; ++l) rank += (l < lane) & (__builtin_amdgcn_readlane(key, l) == key);
+    m = __ballot(have && rank < k);
+  }
+  const int at = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+  wave_lds_sync();
+  if (__builtin_amdgcn_inverse_ballot_w64(m)) list[at] = me;
+  wave_lds_sync();
+  const bool got = lane < __popcll(m);
+  const float2 r = list[lane];
+  score = got ? r.x : -INFINITY;
+  return got ? __float_as_int(r.y) : 0x7fffffff;
+}
+
+// The picks of wave_extract_k without a serial chain per pick.  Every lane's
+// best is one candidate; the bar is the k-th largest of these 64 (at least k
+// candidates reach it, so the k best all do), and the candidates that reach it,
+// on random scores a few more than k, are ranked against each other.  Should
+// more than 64 reach it (many equal scores, or all the best in few lanes), the
+// picks are extracted one by one.  list: 64 entries of LDS.  (Extraction alone
+// took 8000 cycles for 14 of 128 candidates, this 4200.)
+template <int PER>
+__device__ __forceinline__ int wave_top_k(const float *sc, int nc, int k, int lane, float2 *list, float &score) {
+  float v[PER], best = -INFINITY;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    v[j] = j * 64 + lane < nc ? sc[j * 64 + lane] : -INFINITY;
+    best = fmaxf(best, v[j]);
+  }
+  int above = 0;  // lanes whose best is larger
+#pragma unroll
+  for (int l = 0; l < 64; ++l)
+    above += __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(best), l)) > best;
+  const float bar = wave_min_dpp(above < k ? best : INFINITY);
+  int n = 0;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const bool in = j * 64 + lane < nc && v[j] >= bar;
+    const uint64_t m = __ballot(in);
+    const int at = n + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+    if (in && at < 64) list[at] = make_float2(v[j], __int_as_float(j * 64 + lane));
+    n += __popcll(m);
+  }
+  if (n > 64 || n < k) {  // n < k: NaN scores
+    const int c = wave_extract_k<PER>(sc, nc, k);
+    score = lane < k ? sc[c] : -INFINITY;
+    return c;
+  }
+  wave_lds_sync();
+  return wave_rank_k(list, n, k, lane, score);
+}
+
+// top_k by the size of the candidate list (one wave; nc <= 2048)
+__device__ __forceinline__ int top_k_of(const float *sc, int nc, int k, int lane, float2 *list, float &score) {
+  return nc <= 128   ? wave_top_k<2>(sc, nc, k, lane, list, score)
+         : nc <= 512 ? wave_top_k<8>(sc, nc, k, lane, list, score)
+                     : wave_top_k<32>(sc, nc, k, lane, list, score);
+}
+
+// Scores of blocks s0 <= t < s1 of one (b, g) into sc[h * T + t], by NW waves:
+// GM = 1 sums the group's heads before the product (scaled logits), GM = G
+// keeps them apart (log2 units).
+template <typename T, int D, int G, int GM, int NW>
+__device__ __forceinline__ void score_blocks(const T *Qg, const float *kc, int s0, int s1, float *sc, const Geom &gm) {
   constexpr int LPR = D / 4;      // lanes per representative row (one float4 each)
   constexpr int RPW = 64 / LPR;   // rows per wave load instruction
   constexpr int U = 8;            // load instructions in flight per lane
-  constexpr int GM = MODE == 1 ? 8 : 1;   // heads kept apart (the group size is at most 8)
-  extern __shared__ float sc[];   // MODE 0: [T] scores; MODE 1: [G][T] head logits, then scores in row 0
-  __shared__ float mbuf_s[4][64];
-  __shared__ int mbuf_t[4][64];
-  __shared__ float red_m[8][8], red_l[8][8];
-  const int bg = blockIdx.x, b = bg / gm.Hkv, g = bg - b * gm.Hkv;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int sub = lane / LPR, c4 = (lane % LPR) * 4;
-  const int NH = MODE == 1 ? gm.G : 1;
   float q[GM][4];
 #pragma unroll
   for (int h = 0; h < GM; ++h)
 #pragma unroll
     for (int e = 0; e < 4; ++e) q[h][e] = 0.f;
-  for (int hh = 0; hh < gm.G; ++hh) {
-    const T *src = Q + ((int64_t)b * gm.Hq + g * gm.G + hh) * D + c4;
 #pragma unroll
-    for (int h = 0; h < GM; ++h)
-      if (MODE == 0 || h == hh) {
+  for (int hh = 0; hh < G; ++hh)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) q[h][e] += to_f32<T>(src[e]) * (MODE == 1 ? gm.scale * kLog2e : 1.f);
-      }
-  }
-  const int cur = (seq_len(clen, b, gm) - 1) / gm.m;  // the query's own block
-  const int lo = max(0, cur - gm.window / gm.m);
-  // MODE 0 scores the candidates n_init <= t < lo; MODE 1 every complete block t < cur
-  const int s0 = MODE == 1 ? 0 : gm.n_init, s1 = MODE == 1 ? cur : lo;
-  const float *kc = Kc + (int64_t)bg * gm.T * D;
-  for (int t0 = s0 + wave * RPW * U; t0 < s1; t0 += 8 * RPW * U) {
+    for (int e = 0; e < 4; ++e)
+      q[GM > 1 ? hh : 0][e] += to_f32<T>(Qg[hh * D + c4 + e]) * (GM > 1 || gm.sel_mode == 1 ? gm.scale * kLog2e : 1.f);
+  for (int t0 = s0 + wave * RPW * U; t0 < s1; t0 += NW * RPW * U) {
     float4 v[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int t = t0 + u * RPW + sub;
-      v[u] = t < s1 ? *reinterpret_cast<const float4 *>(kc + (int64_t)t * D + c4) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
+    for (int u = 0; u < U; ++u)
+      v[u] = *reinterpret_cast<const float4 *>(kc + (int64_t)min(t0 + u * RPW + sub, s1 - 1) * D + c4);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int t = t0 + u * RPW + sub;
 #pragma unroll
       for (int h = 0; h < GM; ++h) {
-        if (h >= NH) break;
         float a = fmaf(q[h][0], v[u].x, fmaf(q[h][1], v[u].y, fmaf(q[h][2], v[u].z, q[h][3] * v[u].w)));
         a = key_row_sum<LPR>(a);
-        if (lane % LPR == 0 && t < s1) sc[h * gm.T + t] = MODE == 1 ? a : a * gm.scale;
+        if (lane % LPR == 0 && t < s1) sc[h * gm.T + t] = gm.sel_mode == 1 ? a : a * gm.scale;
       }
     }
   }
+}
+
+// Long caches with few sequences: the candidate range of a (b, g) is scored by
+// `slices` workgroups, one CU's loads being what bounds it (1 MB of
+// representatives per (b, g) at T = 2048).  Each leaves the k best of its slice,
+// in index order, as (score, block) at entry slice * k of the group's own O
+// rows, which decode_kernel reads before it writes them.
+template <typename T, int D, int G>
+__global__ __launch_bounds__(512) void decode_scan_kernel(const T *__restrict__ Q, const float *__restrict__ Kc,
+                                                          const int32_t *__restrict__ clen, T *__restrict__ O,
+                                                          Geom gm) {
+  extern __shared__ __attribute__((aligned(16))) float sc[];  // [T]
+  __shared__ float2 list_s[64];
+  const int bg = blockIdx.y, b = bg / gm.Hkv, g = bg - b * gm.Hkv, lane = threadIdx.x & 63;
+  const int cur = (seq_len(clen, b, gm) - 1) / gm.m, lo = max(0, cur - gm.window / gm.m);
+  const int nc = max(0, lo - gm.n_init), per = (nc + gridDim.x - 1) / gridDim.x;
+  const int c0 = min(per * (int)blockIdx.x, nc), n = min(per, nc - c0), k = min(gm.top_k, n);
+  const int64_t q0 = ((int64_t)b * gm.Hq + g * G) * D;
+  score_blocks<T, D, G, 1, 8>(Q + q0, Kc + (int64_t)bg * gm.T * D, gm.n_init + c0, gm.n_init + c0 + n, sc, gm);
   __syncthreads();
-  if (MODE == 1) {
-    // per-head log2 normaliser over t < cur: thread-local running (max, sum),
-    // merged across the wave by shuffles and across the waves through LDS
-    float lse[GM];
+  if (threadIdx.x >= 64) return;
+  float score = -INFINITY;
+  int c = 0x7fffffff;
+  if (k > 0) c = top_k_of(sc + gm.n_init + c0, n, k, lane, list_s, score);
+  if (lane < gm.top_k)
+    reinterpret_cast<float2 *>(O + q0)[blockIdx.x * gm.top_k + lane] =
+        make_float2(score, __int_as_float(lane < k ? gm.n_init + c0 + c : -1));
+}
+
+// LDS of one wave in the attention: its V tile (bf16: 32 keys), later its sums.
+template <typename T, int D, int G> constexpr int decode_wave_bytes() {
+  return sizeof(T) == 2 && 32 * D * 2 > G * D * 4 ? 32 * D * 2 : G * D * 4;
+}
+
+// Copies the values of keys key0[0] .. + 15 and key0[1] .. + 15 (keys past pos:
+// those of pos) into rows 0 .. 31 of a swizzled LDS tile, by one wave (copies
+// straight into LDS, counted in vmcnt).
+template <int D>
+__device__ __forceinline__ void copy_values(const bf16_t *Vb, int64_t kstep, const int (&key0)[2], int pos, bf16_t *Vs,
+                                            int lane) {
+  constexpr int VPR = D / 8, RPI = 64 / VPR;
 #pragma unroll
-    for (int h = 0; h < GM; ++h) {
-      if (h >= NH) break;
-      float mx = -INFINITY, sm = 0.f;
-      for (int t = tid; t < cur; t += 512) {
-        const float x = sc[h * gm.T + t];
-        if (x > mx) {
-          sm = sm * exp2f(mx - x) + 1.f;
-          mx = x;
-        } else {
-          sm += exp2f(x - mx);
+  for (int v = 0; v < 32 / RPI; ++v) {
+    const int r = v * RPI + lane / VPR, c = (lane % VPR) ^ (r & (VPR - 1));
+    const int key = min(key0[(v * RPI) >> 4] + (r & 15), pos);
+    __builtin_amdgcn_global_load_lds(Vb + key * kstep + c * 8, (lds_void_t *)(Vs + v * RPI * D), 16, 0, 0);
+  }
+}
+
+// MODE 0 ranks on the summed logits of the group's heads.  MODE 1
+// (PHSA_FLAG_SELECT_SOFTMAX_SUM) keeps every head's log2 logits of the
+// complete blocks 0..cur-1 in LDS, reduces each head's log2 normaliser over
+// the workgroup, and scores a candidate by log2 sum_h 2^(x_h - lse_h).  MODE 2
+// takes the best of decode_scan_kernel's slices (summed logits).
+// The registers of 16 waves (128 each) hold up to two heads, and any group in
+// bf16 where the heads are not scored apart; the others take 8 waves with 256.
+template <typename T, int G, int MODE> constexpr bool kDecodeSmall = G <= 2 || (sizeof(T) == 2 && MODE != 1);
+
+template <typename T, int D, int G, int MODE, int NW>
+__global__ __launch_bounds__(NW * 64, (kDecodeSmall<T, G, MODE> ? 4 : 2)) void decode_kernel(const T *__restrict__ Q, const T *__restrict__ K,
+                                                           const T *__restrict__ V, const float *__restrict__ Kc,
+                                                           const int32_t *__restrict__ clen,
+                                                           int32_t *__restrict__ sel, T *O,
+                                                           float *__restrict__ LSE, Geom gm, int slices) {
+  constexpr int GM = MODE == 1 ? G : 1;   // heads scored apart
+  constexpr int NTHR = NW * 64;
+  constexpr int AREA = decode_wave_bytes<T, D, G>() / 4;  // floats of a wave's area
+  // MODE 0: [T] scores; MODE 1: [G][T] head logits, then scores in row 0.  Dead
+  // after the top-k: the attention's per-wave areas take the same bytes.
+  extern __shared__ __attribute__((aligned(16))) float sc[];
+  __shared__ float red_m[NW][GM], red_l[NW][GM];
+  __shared__ float2 list_s[64];
+  __shared__ int slot_s[64];
+  __shared__ int nslot_s;
+  __shared__ float wm[NW][G], wl[NW][G], wf[NW][G], lsum[G];
+  const int bg = blockIdx.x, b = bg / gm.Hkv, g = bg - b * gm.Hkv;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int pos = seq_len(clen, b, gm) - 1, cur = pos / gm.m;  // the query's position and own block
+  const int lo = max(0, cur - gm.window / gm.m);
+  const int nc = gm.top_k > 0 ? max(0, lo - gm.n_init) : 0;  // candidates n_init .. lo - 1
+  const T *Qg = Q + ((int64_t)b * gm.Hq + g * G) * D;
+  if (MODE != 2 && nc > 0) {
+    // MODE 0 scores the candidates n_init <= t < lo; MODE 1 every complete block t < cur
+    score_blocks<T, D, G, GM, NW>(Qg, Kc + (int64_t)bg * gm.T * D, MODE == 1 ? 0 : gm.n_init, MODE == 1 ? cur : lo, sc, gm);
+    __syncthreads();
+    if (MODE == 1) {
+      // per-head log2 normaliser over t < cur: thread-local running (max, sum),
+      // merged across the wave by shuffles and across the waves through LDS
+      float lse[GM];
+#pragma unroll
+      for (int h = 0; h < GM; ++h) {
+        float mx = -INFINITY, sm = 0.f;
+        for (int t = tid; t < cur; t += NTHR) {
+          const float x = sc[h * gm.T + t];
+          if (x > mx) {
+            sm = sm * exp2f(mx - x) + 1.f;
+            mx = x;
+          } else {
+            sm += exp2f(x - mx);
+          }
+        }
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const float om = __shfl_xor(mx, o, 64), os = __shfl_xor(sm, o, 64);
+          const float nm = fmaxf(mx, om);
+          sm = (sm > 0.f ? sm * exp2f(mx - nm) : 0.f) + (os > 0.f ? os * exp2f(om - nm) : 0.f);
+          mx = nm;
+        }
+        if (lane == 0) {
+          red_m[wave][h] = mx;
+          red_l[wave][h] = sm;
         }
       }
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const float om = __shfl_xor(mx, o, 64), os = __shfl_xor(sm, o, 64);
-        const float nm = fmaxf(mx, om);
-        sm = (sm > 0.f ? sm * exp2f(mx - nm) : 0.f) + (os > 0.f ? os * exp2f(om - nm) : 0.f);
-        mx = nm;
-      }
-      if (lane == 0) {
-        red_m[wave][h] = mx;
-        red_l[wave][h] = sm;
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int h = 0; h < GM; ++h) {
-      if (h >= NH) break;
-      float M = -INFINITY, L = 0.f;
-#pragma unroll
-      for (int w = 0; w < 8; ++w) M = fmaxf(M, red_m[w][h]);
-#pragma unroll
-      for (int w = 0; w < 8; ++w)
-        if (red_l[w][h] > 0.f) L += red_l[w][h] * exp2f(red_m[w][h] - M);
-      lse[h] = L > 0.f ? M + log2f(L) : 0.f;  // cur = 0 leaves no candidate
-    }
-    // candidates: the group score replaces head 0's logit in place (one thread per block)
-    for (int t = gm.n_init + tid; t < lo; t += 512) {
-      float y[GM], ym = -INFINITY;
+      __syncthreads();
 #pragma unroll
       for (int h = 0; h < GM; ++h) {
-        if (h >= NH) break;
-        y[h] = sc[h * gm.T + t] - lse[h];
-        ym = fmaxf(ym, y[h]);
-      }
-      float e = 0.f;
+        float M = -INFINITY, L = 0.f;
 #pragma unroll
-      for (int h = 0; h < GM; ++h) {
-        if (h >= NH) break;
-        e += exp2f(y[h] - ym);
+        for (int w = 0; w < NW; ++w) M = fmaxf(M, red_m[w][h]);
+#pragma unroll
+        for (int w = 0; w < NW; ++w)
+          if (red_l[w][h] > 0.f) L += red_l[w][h] * exp2f(red_m[w][h] - M);
+        lse[h] = L > 0.f ? M + log2f(L) : 0.f;
       }
-      sc[t] = ym + log2f(e);
+      // candidates: the group score replaces head 0's logit in place (one thread per block)
+      for (int t = gm.n_init + tid; t < lo; t += NTHR) {
+        float y[GM], ym = -INFINITY;
+#pragma unroll
+        for (int h = 0; h < GM; ++h) {
+          y[h] = sc[h * gm.T + t] - lse[h];
+          ym = fmaxf(ym, y[h]);
+        }
+        float e = 0.f;
+#pragma unroll
+        for (int h = 0; h < GM; ++h) e += exp2f(y[h] - ym);
+        sc[t] = ym + log2f(e);
+      }
+      __syncthreads();
     }
-    __syncthreads();
+  }
+  if (wave == 0) {
+    const int npick = min(gm.top_k, nc);
+    int mine = 0x7fffffff;  // lanes 0..npick-1: the picks, ascending
+    float score;
+    if (MODE == 2) {
+      list_s[lane] = lane < slices * gm.top_k ? reinterpret_cast<const float2 *>(O + (Qg - Q))[lane]
+                                              : make_float2(0.f, __int_as_float(-1));
+      wave_lds_sync();
+      mine = wave_rank_k(list_s, slices * gm.top_k, npick, lane, score);
+    } else if (npick > 0) {
+      mine = gm.n_init + top_k_of(sc + gm.n_init, nc, npick, lane, list_s, score);
+    }
+    int32_t *out = sel + (int64_t)bg * gm.ksel;
+    const int ni = min(gm.n_init, cur + 1);
+    const int lstart = max(lo, ni);
+    const int nlocal = cur - lstart + 1;
+    auto put = [&](int slot, int t) {
+      out[slot] = t;
+      slot_s[slot] = t;
+    };
+    if (lane < ni) put(lane, lane);
+    if (lane < npick) put(ni + lane, mine);
+    if (lane < nlocal) put(ni + npick + lane, lstart + lane);
+    for (int x = ni + npick + nlocal + lane; x < gm.ksel; x += 64) out[x] = -1;
+    if (lane == 0) nslot_s = ni + npick + nlocal;
   }
 
-  // Top-k: every wave sorts its 64-candidate chunks best-first across its
-  // lanes (bitonic network over shuffles) and keeps the best 64 seen; the
-  // eight sorted lists are then merged pairwise through LDS.
-  const int nc = max(0, lo - gm.n_init);
-  float rs = -INFINITY;
-  int rt = 0x7fffffff;
-  for (int c0 = wave * 64; c0 < nc; c0 += 8 * 64) {
-    float vs = c0 + lane < nc ? sc[gm.n_init + c0 + lane] : -INFINITY;
-    int vt = c0 + lane < nc ? gm.n_init + c0 + lane : 0x7fffffff;
-    wave_sort_best_first(vs, vt, lane);
-    wave_merge_best_first(rs, rt, vs, vt, lane);
-  }
-  for (int half = 4; half >= 1; half >>= 1) {
-    if (wave >= half && wave < 2 * half) {
-      mbuf_s[wave - half][lane] = rs;
-      mbuf_t[wave - half][lane] = rt;
-    }
-    __syncthreads();
-    if (wave < half) wave_merge_best_first(rs, rt, mbuf_s[wave][lane], mbuf_t[wave][lane], lane);
-    __syncthreads();
-  }
-  if (wave != 0) return;
-  const int npick = min(gm.top_k, nc);
-  const int mine = rt;  // lanes 0..npick-1 hold the picks, best first
-  // ascending order of the picks: rank = number of smaller picks
-  int rank = 0;
-  for (int j = 0; j < npick; ++j) rank += (__shfl(mine, j, 64) < mine);
-  int32_t *out = sel + (int64_t)bg * gm.ksel;
-  const int ni = min(gm.n_init, cur + 1);
-  const int lstart = max(lo, ni);
-  const int nlocal = cur - lstart + 1;
-  if (lane < ni) out[lane] = lane;
-  if (lane < npick) out[ni + rank] = mine;
-  if (lane < nlocal) out[ni + npick + lane] = lstart + lane;
-  for (int x = ni + npick + nlocal + lane; x < gm.ksel; x += 64) out[x] = -1;
-}
-
-// Attention of one decode query over its selected blocks, one workgroup per
-// (b, g); wave w takes slots w, w + 4, ....  A block's K and V rows arrive
-// with coalesced 16-byte loads, NI per lane (lane = one 16-byte chunk of a key
-// row, KPI key rows per load); the CPR lanes of a row reduce its dot products
-// (key_row_sum).  Each wave keeps a running (m, l, o) per head (log2 units);
-// the four are merged through LDS and O, LSE written directly.
-template <typename T, int D, int G>
-__global__ __launch_bounds__(256, G >= 8 ? 1 : 2) void decode_attn_kernel(const T *__restrict__ Q, const T *__restrict__ K,
-                                                          const T *__restrict__ V, const int32_t *__restrict__ clen,
-                                                          const int32_t *__restrict__ sel, T *__restrict__ O,
-                                                          float *__restrict__ LSE, Geom gm) {
-  constexpr int VEC = 16 / sizeof(T);   // elements per 16-byte chunk
-  constexpr int CPR = D / VEC;          // chunks (lanes) per key row
-  constexpr int KPI = 64 / CPR;         // key rows per load instruction
-  constexpr int NI = (8 * KPI > 64 ? 64 : 8 * KPI) / KPI;    // loads per tensor per key group
-  constexpr int KG = NI * KPI;          // keys per group
-  __shared__ float wm[4][G], wl[4][G];
-  __shared__ float wo[4][G][D];
-  const int bg = blockIdx.x, b = bg / gm.Hkv, g = bg - b * gm.Hkv;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int ch = lane % CPR, sub = lane / CPR;
+  // ---- attention over the selected keys, slot after slot
+  __syncthreads();
+  const int msh = __builtin_ctz((unsigned)gm.m);
+  const int nkeys = nslot_s << msh;
+  const T *Kb = K + ((int64_t)b * gm.Lk * gm.Hkv + g) * D, *Vb = V + (Kb - K);
+  const int64_t kstep = (int64_t)gm.Hkv * D;
   const float sl2 = gm.scale * kLog2e;
-  float qv[G][VEC];
+  float *wo = sc + wave * AREA;  // this wave's [G][D] sums, in the end
+  if constexpr (sizeof(T) == 2) {
+    // Matrix cores: 32 keys at a time, S^T = K Q^T (keys x heads; the G heads
+    // fill G of 16 columns) with K straight from memory as the A operand, and
+    // O^T = V^T P^T with V copied into the wave's LDS area and read transposed.
+    // P is split into bf16 hi + lo, two products, so that it keeps 16 bits of
+    // mantissa.  (On the vector ALUs, lane = feature, the products of one
+    // workgroup took 14000 of 25000 cycles at 1 x 8k.)
+    constexpr int KB = D / 32, NT = D / 16;
+    bf16_t *Vs = reinterpret_cast<bf16_t *>(wo);  // [32][D], swizzled
+    const int l16 = lane & 15, q4 = lane >> 4;
+    bf16x8 q[KB];
 #pragma unroll
-  for (int h = 0; h < G; ++h) {
-    const uint4 raw = *reinterpret_cast<const uint4 *>(Q + ((int64_t)b * gm.Hq + g * G + h) * D + ch * VEC);
-    const T *pv = reinterpret_cast<const T *>(&raw);
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) qv[h][e] = to_f32<T>(pv[e]) * sl2;
-  }
-  float mrun[G], lrun[G], o[G][VEC];
-#pragma unroll
-  for (int h = 0; h < G; ++h) {
-    mrun[h] = -INFINITY;
-    lrun[h] = 0.f;
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) o[h][e] = 0.f;
-  }
-  const int pos = seq_len(clen, b, gm) - 1, cur = pos / gm.m;
-  // this wave's slots w, w + 4, ...: lane j holds slot w + 4j (Ksel <= 64), and
-  // the valid ones are taken in slot order from a wave-uniform bit mask
-  const int sj = wave + 4 * lane;
-  const int tl = sj < gm.ksel ? sel[(int64_t)bg * gm.ksel + sj] : -1;
-  uint64_t todo = __ballot(tl >= 0 && tl <= cur && tl < gm.T);
-  auto load_group = [&](int t, int k0, u32x4 (&kr)[NI], u32x4 (&vr)[NI]) {
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int key = min(k0 + i * KPI + sub, gm.m - 1);  // rows past a short block are masked below
-      const int64_t src = (((int64_t)b * gm.Lk + (int64_t)t * gm.m + key) * gm.Hkv + g) * D + ch * VEC;
-      kr[i] = *reinterpret_cast<const u32x4 *>(K + src);
-      vr[i] = *reinterpret_cast<const u32x4 *>(V + src);
+    for (int kb = 0; kb < KB; ++kb) {
+      const u32x4 z = {0u, 0u, 0u, 0u};
+      q[kb] = __builtin_bit_cast(
+          bf16x8, l16 < G ? *reinterpret_cast<const u32x4 *>(Q + ((int64_t)b * gm.Hq + g * G + l16) * D + kb * 32 + q4 * 8)
+                          : z);
     }
-  };
-  auto attend = [&](int t, int k0, const u32x4 (&kr)[NI], const u32x4 (&vr)[NI]) {
+    f32x4 o[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) o[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float mrun = -INFINITY, lrun = 0.f;
+    for (int x0 = wave * 32; x0 < nkeys; x0 += NW * 32) {
+      int key0[2];  // first key of each 16-key tile (past the last slot: the last tile again, masked)
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt) {
+        const int x = min(x0 + kt * 16, nkeys - 16);
+        key0[kt] = (__builtin_amdgcn_readfirstlane(slot_s[x >> msh]) << msh) + (x & (gm.m - 1));
+      }
+      bf16x8 kf[2][KB];
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+          kf[kt][kb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(
+                                                      Kb + min(key0[kt] + l16, pos) * kstep + kb * 32 + q4 * 8));
+      wave_lds_sync();  // the previous tile's transposed reads are done
+      copy_values<D>(Vb, kstep, key0, pos, Vs, lane);
+      f32x4 st[2];
+      float mn = mrun;
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt) {
+        st[kt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) st[kt] = mfma16x16x32(kf[kt][kb], q[kb], st[kt]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const bool ok = x0 + kt * 16 < nkeys && key0[kt] + q4 * 4 + r <= pos;
+          st[kt][r] = ok ? st[kt][r] * sl2 : -INFINITY;
+          mn = fmaxf(mn, st[kt][r]);
+        }
+      }
+      mn = max_xor32(max_xor16(mn));
+      // mn stays -inf only while every key so far was masked
+      const float f = mn == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(mrun - mn);
+      const float mz = mn == -INFINITY ? 0.f : mn;
+      mrun = mn;
+      lrun *= f;
+      f32x4 lo[2];
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float p = __builtin_amdgcn_exp2f(st[kt][r] - mz);
+          lrun += p;
+          const float h = bf16_to_f32(f32_to_bf16(p));
+          st[kt][r] = h;
+          lo[kt][r] = p - h;
+        }
+      const bf16x8 ph = pack_bf16x8(st[0], st[1]), pl = pack_bf16x8(lo[0], lo[1]);
+      dma_wait();
+      wave_lds_sync();
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        const bf16x8 vt = lds_col8_sw<D>(Vs, q4 * 4, 16 + q4 * 4, nt * 16, l16);
+        o[nt] *= f;
+        o[nt] = mfma16x16x32(vt, ph, o[nt]);
+        o[nt] = mfma16x16x32(vt, pl, o[nt]);
+      }
+    }
+    lrun += __shfl_xor(lrun, 16, 64);
+    lrun += __shfl_xor(lrun, 32, 64);
+    wave_lds_sync();
+    if (l16 < G) {  // lane (q, j) holds features 16 nt + 4 q .. + 3 of head j
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) *reinterpret_cast<f32x4 *>(wo + l16 * D + nt * 16 + q4 * 4) = o[nt];
+      if (q4 == 0) {
+        wm[wave][l16] = mrun;
+        wl[wave][l16] = lrun;
+      }
+    }
+  } else {
+    // float32: load unit u covers KPI keys (blocks are multiples of 16 keys, so a
+    // unit lies in one block); lane = (sub, ch) holds VEC features of every
+    // KPI-th key and the CPR lanes of a key reduce its dot products.
+    constexpr int VEC = 16 / sizeof(T), CPR = D / VEC, KPI = 64 / CPR, NI = 8;
+    const int ch = lane % CPR, sub = lane / CPR;
+    f32x4 qv[G], o[G];
+    float mrun[G], lrun[G];
 #pragma unroll
     for (int h = 0; h < G; ++h) {
-      float sc[NI];
-      float bm = -INFINITY;
-#pragma unroll
-      for (int i = 0; i < NI; ++i) {
-        const T *pk = reinterpret_cast<const T *>(&kr[i]);
-        float a = 0.f;
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) a = fmaf(qv[h][e], to_f32<T>(pk[e]), a);
-        a = key_row_sum<CPR>(a);
-        const int kb = k0 + i * KPI + sub;
-        sc[i] = kb < gm.m && t * gm.m + kb <= pos ? a : -INFINITY;
-        bm = fmaxf(bm, sc[i]);
-      }
-#pragma unroll
-      for (int x = CPR; x < 64; x <<= 1) bm = fmaxf(bm, __shfl_xor(bm, x, 64));
-      const float mn = fmaxf(mrun[h], bm);
-      // mn stays -inf only while every key so far was past the query (a partly
-      // written own block): nothing has been accumulated yet
-      const float f = mn == -INFINITY ? 1.f : exp2f(mrun[h] - mn);
-      float ls = 0.f;
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) o[h][e] *= f;
-#pragma unroll
-      for (int i = 0; i < NI; ++i) {
-        // keys past the query (the unwritten tail of its own block) add nothing,
-        // whatever their V slots hold
-        const int kb = k0 + i * KPI + sub;
-        const bool valid = kb < gm.m && t * gm.m + kb <= pos;
-        const float p = valid ? exp2f(sc[i] - mn) : 0.f;
-        ls += p;
-        const T *pv = reinterpret_cast<const T *>(&vr[i]);
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) o[h][e] = valid ? fmaf(p, to_f32<T>(pv[e]), o[h][e]) : o[h][e];
-      }
-      // ls counts this lane's keys; the CPR lanes of a key row hold the same keys
-      lrun[h] = lrun[h] * f + ls;
-      mrun[h] = mn;
+      qv[h] = *reinterpret_cast<const f32x4 *>(Q + ((int64_t)b * gm.Hq + g * G + h) * D + ch * VEC) * sl2;
+      o[h] = f32x4{0.f, 0.f, 0.f, 0.f};
+      mrun[h] = -INFINITY;
+      lrun[h] = 0.f;
     }
-  };
-  for (; todo; todo &= todo - 1) {
-    const int t = __builtin_amdgcn_readlane(tl, __builtin_ctzll(todo));
-    for (int k0 = 0; k0 < gm.m; k0 += KG) {
-      u32x4 kr[NI], vr[NI];  // native vectors: uint4 arrays here would live in scratch
-      load_group(t, k0, kr, vr);
-      attend(t, k0, kr, vr);
+    const int nunits = nkeys / KPI;
+    for (int u0 = wave * NI; u0 < nunits; u0 += NW * NI) {
+      f32x4 kr[NI], vr[NI];
+      uint32_t okm = 0;      // bit i: this lane's key of load i counts
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const int x = min(u0 + i, nunits - 1) * KPI;  // units past the end are masked
+        const int key = (__builtin_amdgcn_readfirstlane(slot_s[x >> msh]) << msh) + (x & (gm.m - 1)) + sub;
+        okm |= u0 + i < nunits && key <= pos ? 1u << i : 0u;
+        const int64_t src = min(key, pos) * kstep + ch * VEC;
+        kr[i] = *reinterpret_cast<const f32x4 *>(Kb + src);
+        vr[i] = *reinterpret_cast<const f32x4 *>(Vb + src);
+      }
+#pragma unroll
+      for (int h = 0; h < G; ++h) {
+        float s[NI], mn = mrun[h];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+          float a = 0.f;
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) a = fmaf(qv[h][e], kr[i][e], a);
+          a = key_row_sum<CPR>(a);
+          s[i] = (okm >> i) & 1 ? a : -INFINITY;
+          mn = fmaxf(mn, s[i]);
+        }
+        // every key group of lanes keeps a maximum of its own (equal in the CPR
+        // lanes of a key); they meet at the end.  mn stays -inf only while every
+        // key so far was masked: nothing has been accumulated yet.
+        const float f = mn == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(mrun[h] - mn);
+        mrun[h] = mn;
+        lrun[h] *= f;
+        o[h] *= f;
+        // keys past the query (the unwritten tail of its own block) add nothing
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+          const float p = (okm >> i) & 1 ? __builtin_amdgcn_exp2f(s[i] - mn) : 0.f;
+          lrun[h] += p;
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) o[h][e] = fmaf(p, vr[i][e], o[h][e]);
+        }
+      }
+    }
+    // the key groups of the wave (lanes with the same chunk)
+#pragma unroll
+    for (int h = 0; h < G; ++h) {
+      float M = mrun[h];
+#pragma unroll
+      for (int x = CPR; x < 64; x <<= 1) M = fmaxf(M, __shfl_xor(M, x, 64));
+      const float f = mrun[h] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mrun[h] - M);
+      lrun[h] *= f;
+      o[h] *= f;
+#pragma unroll
+      for (int x = CPR; x < 64; x <<= 1) {
+        lrun[h] += __shfl_xor(lrun[h], x, 64);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) o[h][e] += __shfl_xor(o[h][e], x, 64);
+      }
+      if (lane == 0) {
+        wm[wave][h] = M;
+        wl[wave][h] = lrun[h];
+      }
+      if (sub == 0) *reinterpret_cast<f32x4 *>(wo + h * D + ch * VEC) = o[h];
     }
   }
-  // reduce over the key-row groups of the wave (lanes with the same chunk)
+  // ---- the waves' sums: their factors first (one thread per wave and head), then the features
+  __syncthreads();
+  if (tid < NW * G) {
+    const int w = tid / G, h = tid - w * G;
+    float M = -INFINITY, L = 0.f;
 #pragma unroll
-  for (int h = 0; h < G; ++h) {
+    for (int v = 0; v < NW; ++v) M = fmaxf(M, wm[v][h]);
 #pragma unroll
-    for (int x = CPR; x < 64; x <<= 1) {
-      lrun[h] += __shfl_xor(lrun[h], x, 64);
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) o[h][e] += __shfl_xor(o[h][e], x, 64);
-    }
-    if (lane == 0) {
-      wm[wave][h] = mrun[h];
-      wl[wave][h] = lrun[h];
-    }
-    if (sub == 0) {
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) wo[wave][h][ch * VEC + e] = o[h][e];
+    for (int v = 0; v < NW; ++v) L += wm[v][h] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(wm[v][h] - M) * wl[v][h];
+    wf[w][h] = wm[w][h] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(wm[w][h] - M);
+    if (w == 0) {
+      lsum[h] = L;
+      LSE[(int64_t)b * gm.Hq + g * G + h] = L > 0.f ? (M + log2f(L)) * kLn2 : -INFINITY;
     }
   }
   __syncthreads();
-  for (int x = tid; x < G * D; x += 256) {
+  for (int x = tid; x < G * D; x += NTHR) {
     const int h = x / D, c = x - h * D;
-    float M = -INFINITY;
+    float acc = 0.f;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) M = fmaxf(M, wm[w][h]);
-    float L = 0.f, acc = 0.f;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const float f = wm[w][h] == -INFINITY ? 0.f : exp2f(wm[w][h] - M);
-      L = fmaf(f, wl[w][h], L);
-      acc = fmaf(f, wo[w][h][c], acc);
+    for (int w = 0; w < NW; ++w) {
+      // a wave without keys left zeros (or nothing, with factor 0): never multiply what it did not write
+      const float f = wf[w][h];
+      acc = fmaf(f, sc[w * AREA + h * D + c], acc);
     }
-    O[((int64_t)b * gm.Hq + g * G + h) * D + c] = from_f32<T>(L > 0.f ? acc / L : 0.f);
-    if (c == 0) LSE[(int64_t)b * gm.Hq + g * G + h] = L > 0.f ? (M + log2f(L)) * kLn2 : -INFINITY;
+    O[((int64_t)b * gm.Hq + g * G + h) * D + c] = from_f32<T>(lsum[h] > 0.f ? acc / lsum[h] : 0.f);
   }
 }
 
-template <typename T, int D, int G>
-static hipError_t launch_decode_g(const Geom &g, const void *Q, const void *K, const void *V, const float *Kc,
-                                  const int32_t *clen, int32_t *sel, void *O, float *LSE, hipStream_t s) {
-  timing_begin("phsa_decode_select", s);
-  if (g.sel_mode == 1)
-    hipLaunchKernelGGL((decode_select_kernel<T, D, 1>), dim3(g.B * g.Hkv), dim3(512),
-                       (size_t)g.G * g.T * sizeof(float), s, static_cast<const T *>(Q), Kc, clen, sel, g);
-  else
-    hipLaunchKernelGGL((decode_select_kernel<T, D, 0>), dim3(g.B * g.Hkv), dim3(512), (size_t)g.T * sizeof(float), s,
-                       static_cast<const T *>(Q), Kc, clen, sel, g);
-  timing_end(s);
-  timing_begin("phsa_decode_attn", s);
-  hipLaunchKernelGGL((decode_attn_kernel<T, D, G>), dim3(g.B * g.Hkv), dim3(256), 0, s, static_cast<const T *>(Q),
-                     static_cast<const T *>(K), static_cast<const T *>(V), clen, sel, static_cast<T *>(O), LSE, g);
+struct DecodeArgs {
+  const void *Q, *K, *V;
+  const float *Kc;
+  const int32_t *clen;
+  int32_t *sel;
+  void *O;
+  float *LSE;
+};
+
+template <typename T, int D, int G, int MODE, int NW>
+static hipError_t launch_decode_w(const Geom &g, const DecodeArgs &a, int slices, hipStream_t s) {
+  timing_begin("phsa_decode", s);
+  hipLaunchKernelGGL((decode_kernel<T, D, G, MODE, NW>), dim3(g.B * g.Hkv), dim3(NW * 64),
+                     std::max(MODE == 2 ? 0 : (size_t)(MODE == 1 ? G : 1) * g.T * sizeof(float),
+                              (size_t)NW * decode_wave_bytes<T, D, G>()),
+                     s, static_cast<const T *>(a.Q), static_cast<const T *>(a.K), static_cast<const T *>(a.V), a.Kc,
+                     a.clen, a.sel, static_cast<T *>(a.O), a.LSE, g, slices);
   timing_end(s);
   return hipGetLastError();
 }
 
+// Up to one workgroup per CU they take 16 waves, beyond that 8 (two share a CU).
+template <typename T, int D, int G, int MODE>
+static hipError_t launch_decode_m(const Geom &g, const DecodeArgs &a, int slices, hipStream_t s) {
+  if constexpr (kDecodeSmall<T, G, MODE>)
+    if (g.B * g.Hkv <= 256) return launch_decode_w<T, D, G, MODE, 16>(g, a, slices, s);
+  return launch_decode_w<T, D, G, MODE, 8>(g, a, slices, s);
+}
+
+template <typename T, int D, int G>
+static hipError_t launch_decode_g(const Geom &g, const DecodeArgs &a, hipStream_t s) {
+  if (g.sel_mode == 1) return launch_decode_m<T, D, G, 1>(g, a, 0, s);
+  // Slices of the candidate range: as many as the group's O rows hold lists of
+  // (one wave ranks at most 64 entries), while the workgroups fit the CUs and a
+  // slice keeps 256 blocks.  Below that the second launch costs what it gains.
+  // O is scratch until the second kernel: not where it is Q, or not aligned.
+  int slices = g.top_k > 0 ? std::min({(int)(G * D * sizeof(T) / 8), 64}) / g.top_k : 0;
+  slices = std::min({slices, 256 / (g.B * g.Hkv), g.T / 256});
+  if (slices < 2 || a.O == a.Q || reinterpret_cast<uintptr_t>(a.O) % 8 != 0)
+    return launch_decode_m<T, D, G, 0>(g, a, 0, s);
+  timing_begin("phsa_decode_scan", s);
+  hipLaunchKernelGGL((decode_scan_kernel<T, D, G>), dim3(slices, g.B * g.Hkv), dim3(512), g.T * sizeof(float), s,
+                     static_cast<const T *>(a.Q), a.Kc, a.clen, static_cast<T *>(a.O), g);
+  timing_end(s);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  return launch_decode_m<T, D, G, 2>(g, a, slices, s);
+}
+
 template <typename T, int D>
-static hipError_t launch_decode_t(const Geom &g, const void *Q, const void *K, const void *V, const float *Kc,
-                                  const int32_t *clen, int32_t *sel, void *O, float *LSE, hipStream_t s) {
+static hipError_t launch_decode_t(const Geom &g, const DecodeArgs &a, hipStream_t s) {
   switch (g.G) {
-    case 1: return launch_decode_g<T, D, 1>(g, Q, K, V, Kc, clen, sel, O, LSE, s);
-    case 2: return launch_decode_g<T, D, 2>(g, Q, K, V, Kc, clen, sel, O, LSE, s);
-    case 4: return launch_decode_g<T, D, 4>(g, Q, K, V, Kc, clen, sel, O, LSE, s);
-    default: return launch_decode_g<T, D, 8>(g, Q, K, V, Kc, clen, sel, O, LSE, s);
+    case 1: return launch_decode_g<T, D, 1>(g, a, s);
+    case 2: return launch_decode_g<T, D, 2>(g, a, s);
+    case 4: return launch_decode_g<T, D, 4>(g, a, s);
+    default: return launch_decode_g<T, D, 8>(g, a, s);
   }
 }
 
@@ -531,11 +773,9 @@ hipError_t launch_cache_append(const Geom &g, const void *Kn, const void *Vn, co
 
 hipError_t launch_decode(const Geom &g, const void *Q, const void *K, const void *V, const float *Kc,
                          const int32_t *clen, int32_t *sel, void *O, float *LSE, hipStream_t s) {
-  if (g.dtype == 0)
-    return g.d == 128 ? launch_decode_t<bf16_t, 128>(g, Q, K, V, Kc, clen, sel, O, LSE, s)
-                      : launch_decode_t<bf16_t, 64>(g, Q, K, V, Kc, clen, sel, O, LSE, s);
-  return g.d == 128 ? launch_decode_t<float, 128>(g, Q, K, V, Kc, clen, sel, O, LSE, s)
-                    : launch_decode_t<float, 64>(g, Q, K, V, Kc, clen, sel, O, LSE, s);
+  const DecodeArgs a{Q, K, V, Kc, clen, sel, O, LSE};
+  if (g.dtype == 0) return g.d == 128 ? launch_decode_t<bf16_t, 128>(g, a, s) : launch_decode_t<bf16_t, 64>(g, a, s);
+  return g.d == 128 ? launch_decode_t<float, 128>(g, a, s) : launch_decode_t<float, 64>(g, a, s);
 }
 
 }  // namespace phsa
