@@ -668,21 +668,24 @@ static hipError_t launch_decode_t(const Geom &g, const DecodeArgs &a, hipStream_
 // written to K_comp[b, :, t].  One workgroup per sequence; a sequence whose
 // cache is full is left unchanged.  Rows move in 16-byte chunks; for the
 // pooling, the Hkv*d elements are split into 16-byte chunks and the block's m
-// keys into 256 / #chunks slices, whose partial sums meet in LDS.
+// keys into NTHR / #chunks slices, U rows in flight per thread, whose partial
+// sums meet in LDS.  A chain of memory round trips bounds it (length, row,
+// block), so the block's punctuation flags are one load and a ballot per wave
+// (one thread counting them a byte at a time took the call from 7 to 30 us).
 template <typename T, int D>
-__global__ __launch_bounds__(256) void cache_append_kernel(const T *__restrict__ Kn, const T *__restrict__ Vn,
-                                                           const uint8_t *__restrict__ pn, T *__restrict__ Kcache,
-                                                           T *__restrict__ Vcache, uint8_t *__restrict__ pcache,
-                                                           int32_t *__restrict__ clen, float *__restrict__ Kc,
-                                                           Geom gm) {
-  constexpr int VEC = 16 / sizeof(T);
-  __shared__ float red[2][256][VEC];
-  __shared__ int npun;
-  const int b = blockIdx.x, tid = threadIdx.x;
+__global__ __launch_bounds__(1024) void cache_append_kernel(const T *__restrict__ Kn, const T *__restrict__ Vn,
+                                                            const uint8_t *__restrict__ pn, T *__restrict__ Kcache,
+                                                            T *__restrict__ Vcache, uint8_t *__restrict__ pcache,
+                                                            int32_t *__restrict__ clen, float *__restrict__ Kc,
+                                                            Geom gm) {
+  constexpr int VEC = 16 / sizeof(T), NTHR = 1024, U = 8;
+  __shared__ float red[2][NTHR][VEC];
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
   const int pos = clen[b];
   if (pos < 0 || pos >= gm.Lk) return;  // full (or invalid): nothing changes
   const int HD = gm.Hkv * D, NCH = HD / VEC;
-  for (int x = tid; x < NCH; x += 256) {
+  const bool newp = pn[b] != 0;
+  for (int x = tid; x < NCH; x += NTHR) {
     const int64_t dst = ((int64_t)b * gm.Lk + pos) * HD + x * VEC;
     *reinterpret_cast<uint4 *>(Kcache + dst) = *reinterpret_cast<const uint4 *>(Kn + (int64_t)b * HD + x * VEC);
     *reinterpret_cast<uint4 *>(Vcache + dst) = *reinterpret_cast<const uint4 *>(Vn + (int64_t)b * HD + x * VEC);
@@ -692,31 +695,38 @@ __global__ __launch_bounds__(256) void cache_append_kernel(const T *__restrict__
     // the block is complete: pool its m keys (the newest one from the input,
     // the others from the cache, which this launch does not write)
     const int t = pos / gm.m, j0 = t * gm.m;
-    if (tid == 0) {
-      int c = 0;
-      for (int j = j0; j < j0 + gm.m; ++j) c += (j == pos ? pn[b] : pcache[(int64_t)b * gm.Lk + j]) != 0;
-      npun = c;
-    }
-    for (int x0 = 0; x0 < NCH; x0 += 256) {
-      const int nch = min(256, NCH - x0);       // chunks handled in this pass
-      const int slices = 256 / nch;             // key slices
+    // flags of the block's keys, in every wave (attention blocks hold at most 64)
+    const bool flag = lane < gm.m && (j0 + lane == pos ? newp : pcache[(int64_t)b * gm.Lk + j0 + min(lane, gm.m - 1)] != 0);
+    const uint64_t pmask = __ballot(flag);
+    const int np = __popcll(pmask);
+    for (int x0 = 0; x0 < NCH; x0 += NTHR) {
+      const int nch = min(NTHR, NCH - x0);      // chunks handled in this pass
+      const int slices = NTHR / nch;            // key slices
       const int ch = tid % nch, sl = tid / nch;
       float sum[VEC], psum[VEC];
 #pragma unroll
       for (int e = 0; e < VEC; ++e) sum[e] = psum[e] = 0.f;
       if (sl < slices) {
-        for (int j = j0 + sl; j < j0 + gm.m; j += slices) {
-          const bool newest = j == pos;
-          const uint4 raw = newest ? *reinterpret_cast<const uint4 *>(Kn + (int64_t)b * HD + (x0 + ch) * VEC)
-                                   : *reinterpret_cast<const uint4 *>(Kcache + ((int64_t)b * gm.Lk + j) * HD +
-                                                                      (x0 + ch) * VEC);
-          const bool pj = (newest ? pn[b] : pcache[(int64_t)b * gm.Lk + j]) != 0;
-          const T *pv = reinterpret_cast<const T *>(&raw);
+        for (int ja = sl; ja < gm.m; ja += U * slices) {
+          u32x4 raw[U];
 #pragma unroll
-          for (int e = 0; e < VEC; ++e) {
-            const float k = to_f32<T>(pv[e]);
-            sum[e] += k;
-            psum[e] += pj ? k : 0.f;
+          for (int u = 0; u < U; ++u) {
+            const int j = j0 + min(ja + u * slices, gm.m - 1);
+            raw[u] = *reinterpret_cast<const u32x4 *>(
+                j == pos ? Kn + (int64_t)b * HD + (x0 + ch) * VEC : Kcache + ((int64_t)b * gm.Lk + j) * HD + (x0 + ch) * VEC);
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int j = ja + u * slices;
+            if (j >= gm.m) break;
+            const bool pj = lane_bit(pmask, j);
+            const T *pv = reinterpret_cast<const T *>(&raw[u]);
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) {
+              const float k = to_f32<T>(pv[e]);
+              sum[e] += k;
+              psum[e] += pj ? k : 0.f;
+            }
           }
         }
       }
@@ -727,7 +737,6 @@ __global__ __launch_bounds__(256) void cache_append_kernel(const T *__restrict__
       }
       __syncthreads();
       if (tid < nch) {
-        const int np = npun;
         float rep[VEC];
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {
@@ -755,7 +764,7 @@ template <typename T, int D>
 static hipError_t launch_cache_append_t(const Geom &g, const void *Kn, const void *Vn, const uint8_t *pn, void *Kcache,
                                         void *Vcache, uint8_t *pcache, int32_t *clen, float *Kc, hipStream_t s) {
   timing_begin("phsa_cache_append", s);
-  hipLaunchKernelGGL((cache_append_kernel<T, D>), dim3(g.B), dim3(256), 0, s, static_cast<const T *>(Kn),
+  hipLaunchKernelGGL((cache_append_kernel<T, D>), dim3(g.B), dim3(1024), 0, s, static_cast<const T *>(Kn),
                      static_cast<const T *>(Vn), pn, static_cast<T *>(Kcache), static_cast<T *>(Vcache), pcache, clen,
                      Kc, g);
   timing_end(s);
