@@ -708,9 +708,9 @@ __global__ __launch_bounds__(256) void select_softmax_mfma_kernel(const bf16_t *
 // made on these sums before the (positive) softmax scale, which orders the
 // blocks the same way.
 //
-// Tiling.  A workgroup of NW waves takes 32 NW query rows of one (b, g); wave
-// w owns two 16-row tiles (rows 32w..32w+31), so every representative fragment
-// read from LDS feeds two MFMAs, and one staged chunk of CH representatives
+// Tiling.  A workgroup of NW waves takes 16 RT NW query rows of one (b, g); wave
+// w owns RT 16-row tiles (two: rows 32w..32w+31; one in small problems), so every
+// representative fragment read from LDS feeds RT MFMAs, and one staged chunk of CH representatives
 // serves all rows of the workgroup.  Chunks are copied from global memory
 // straight into swizzled LDS tiles (global_load_lds); pass 1 keeps the next
 // chunk(s) in flight, pass 2 one or two (hi, lo) pairs (DB).  With k <= 16
@@ -870,14 +870,13 @@ __device__ __noinline__ int compact_list(float2 *lp, int n, int k, float *ks) {
   return pos;
 }
 
-template <int D, int G, int KMAXK, int NW, bool DB, int CH>
+template <int D, int G, int KMAXK, int NW, bool DB, int CH, int RT>
 __global__ __launch_bounds__(NW * 64) void select_mfma_kernel(const bf16_t *__restrict__ Q,
                                                               const bf16_t *__restrict__ Mh_g,
                                                               const bf16_t *__restrict__ Ml_g,
                                                               const float2 *__restrict__ Mnorm_g,
                                                               int32_t *__restrict__ sel, Geom gm) {
   constexpr int NT = CH / 16;             // 16-block columns per chunk of CH blocks
-  constexpr int RT = 2;                   // 16-row tiles per wave (B fragments are reused across them)
   constexpr int ROWS = NW * 16 * RT;      // query rows per workgroup
   constexpr int NR = 4 * RT;              // rows per lane in the accumulator layout
   constexpr int MP = D + 8;               // LDS pitch of a staged representative (sizes the staging area)
@@ -1337,13 +1336,24 @@ static hipError_t launch_select_mfma(const Geom &g, const void *Q, const float *
                      n / 8);
   timing_end(s);
   timing_begin("phsa_select", s);
-  if (g.top_k <= 16) {
+  // With fewer than the 512 workgroups of 128 rows that the chip holds at once,
+  // a workgroup's own chain (bar, appends and final rank of each wave's rows) is
+  // the kernel's duration: one row tile per wave, 64 rows per workgroup (1k
+  // rows 26 -> 16 us, 1000 rows against 320 blocks 47 -> 30 us; at 512 workgroups
+  // even, at T = 2048 2.08 ms against 1.68: a staged chunk then serves half as
+  // many rows).
+  const int64_t wgs = (int64_t)((g.Lq + 127) / 128) * g.B * g.Hkv;
+  if (g.top_k <= 16 && wgs < 512) {
+    const dim3 grid((g.Lq + 63) / 64, g.B * g.Hkv);
+    hipLaunchKernelGGL((select_mfma_kernel<D, G, 16, 4, false, 64, 1>), grid, dim3(256), 0, s,
+                       static_cast<const bf16_t *>(Q), mh, ml, mnorm, sel, g);
+  } else if (g.top_k <= 16) {
     const dim3 grid((g.Lq + PHSA_SEL_NW * 32 - 1) / (PHSA_SEL_NW * 32), g.B * g.Hkv);
-    hipLaunchKernelGGL((select_mfma_kernel<D, G, 16, PHSA_SEL_NW, PHSA_SEL_DB, PHSA_SEL_CH>), grid, dim3(PHSA_SEL_NW * 64), 0, s,
+    hipLaunchKernelGGL((select_mfma_kernel<D, G, 16, PHSA_SEL_NW, PHSA_SEL_DB, PHSA_SEL_CH, 2>), grid, dim3(PHSA_SEL_NW * 64), 0, s,
                        static_cast<const bf16_t *>(Q), mh, ml, mnorm, sel, g);
   } else {
     const dim3 grid((g.Lq + 255) / 256, g.B * g.Hkv);
-    hipLaunchKernelGGL((select_mfma_kernel<D, G, 32, 8, false, 64>), grid, dim3(512), 0, s,
+    hipLaunchKernelGGL((select_mfma_kernel<D, G, 32, 8, false, 64, 2>), grid, dim3(512), 0, s,
                        static_cast<const bf16_t *>(Q), mh, ml, mnorm, sel, g);
   }
   timing_end(s);
