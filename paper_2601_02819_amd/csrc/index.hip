@@ -22,8 +22,9 @@
 // Integer-only passes, all deterministic (no order depends on timing):
 //   count : per 256-row tile, an LDS bitmap [8 words][T] of who selected
 //           what; popcounts give per-tile counts cntw[bg][w][t].
-//   scan  : one workgroup per bg: per t the exclusive prefix over tiles -> toff
-//           and the total -> cnt; over t the list and unit offsets and the unit tables.
+//   scan  : one workgroup per bg: per t the exclusive prefix over tiles -> toff,
+//           over t the list and unit offsets and the unit tables (with few
+//           counts the fill's workgroups do this themselves).
 //   fill  : rebuilds the tile bitmap; an entry's place in its list is
 //           tile offset + number of lower rows in the tile that chose t.
 #include "common.h"
@@ -36,10 +37,10 @@ __device__ __forceinline__ bool slot_valid(int t, int cur, int T) { return t >= 
 // Width of a sel row: the selection's own Ksel (in its block units).
 __device__ __forceinline__ int sel_width(const Geom &gm) { return gm.n_init + gm.window / gm.sm + 1 + gm.top_k; }
 
-// Selections of 64-token blocks are indexed one thread per row: a row's
-// entries are the valid prefix of its sel row (ascending causal blocks, ended
-// by -1 or a block past the query's own), less its forced blocks when the
-// band takes them.
+// A selection whose blocks are the index's own: a row's entries are the valid
+// prefix of its sel row (ascending causal blocks, ended by -1 or a block past
+// the query's own), less its forced blocks when the band takes them (then one
+// thread per row; without a band by (row, slot) pairs).
 __device__ __forceinline__ bool plain_rows(const Geom &gm) { return gm.sm == gm.m; }
 
 // The forced blocks of Algorithm 1 for the query in block cur: the init blocks
@@ -239,8 +240,8 @@ struct ListCounts {
 
 constexpr int kScanThreads = 512;
 
-// Exclusive scan of v over the workgroup (each field on its own); tot receives
-// the workgroup's sums.  Holds barriers.
+// Exclusive scan of v over a workgroup of kScanThreads (each field on its own);
+// tot receives the workgroup's sums.  Holds barriers.
 __device__ __forceinline__ ListCounts block_scan(ListCounts v, ListCounts &tot) {
   constexpr int NW = kScanThreads / 64;
   __shared__ ListCounts wsum_s[NW];
@@ -266,14 +267,18 @@ __device__ __forceinline__ ListCounts block_scan(ListCounts v, ListCounts &tot) 
   return ListCounts{pre.c + inc.c - v.c, pre.nu + inc.nu - v.nu, pre.f + inc.f - v.f, pre.nf + inc.nf - v.nf};
 }
 
-// One workgroup per bg: per t the exclusive prefix of the tile counts (toff),
-// then over t the list offsets, the unit tables and the finalize list.  Every
-// bg keeps its lists and units in regions of its own, so no prefix crosses
-// workgroups and one launch does it.  tp (a power of two) threads cover the
-// blocks; with few blocks the kScanThreads / tp thread groups share the tiles.
-__global__ __launch_bounds__(kScanThreads) void index_scan_kernel(Geom gm, IndexWs ix, int tp) {
+// The lists of one bg, by a workgroup: per t the exclusive prefix of the tile
+// counts, then over t the list offsets, the unit tables and the finalize list.
+// Every bg keeps its lists and units in regions of its own, so no prefix crosses
+// bg.  tp (a power of two) threads cover the blocks; with few blocks the
+// kScanThreads / tp thread groups share the tiles.
+//   base_s null: writes the tile prefixes (toff), the list offsets and the tables.
+//   base_s given: base_s[t] = list position of the first entry of tile w_own; the
+//                 tables are written by the workgroup of tile 0 alone.
+__device__ __forceinline__ void scan_lists(const Geom &gm, const IndexWs &ix, int bg, int tp, int w_own, int32_t *base_s) {
   __shared__ int part_s[kScanThreads];
-  const int bg = blockIdx.x, tid = threadIdx.x;
+  const int tid = threadIdx.x;
+  const bool tables = !base_s || w_own == 0;
   const int32_t *cw = ix.cntw + (int64_t)bg * ix.W * gm.T;
   int32_t *to = ix.toff + (int64_t)bg * ix.W * gm.T;
   int2 *fu = ix.funits + (int64_t)bg * ix.funits_bg;
@@ -309,7 +314,10 @@ __global__ __launch_bounds__(kScanThreads) void index_scan_kernel(Geom gm, Index
 #pragma unroll
       for (int u = 0; u < U; ++u)
         if (w + u < w1) {
-          if (t < gm.T) to[(int64_t)(w + u) * gm.T + t] = run;
+          if (t < gm.T) {
+            if (!base_s) to[(int64_t)(w + u) * gm.T + t] = run;
+            else if (w + u == w_own) base_s[t] = run;
+          }
           run += c[u];
         }
     }
@@ -328,22 +336,125 @@ __global__ __launch_bounds__(kScanThreads) void index_scan_kernel(Geom gm, Index
     at.add(carry);
     if (live) {
       const int x = bg * gm.T + t;
-      ix.off[x] = at.c;
-      ix.uoff[(int64_t)bg * (gm.T + 1) + t] = at.nu;
-      for (int u = 0; u < nu; ++u)
-        un[at.nu + u] =
-            make_int4(x, min(ix.unit_tokens, run - u * ix.unit_tokens), at.c + u * ix.unit_tokens, nu == 1 ? 1 : 0);
-      if (v.f) ix.fin[(int64_t)bg * gm.T + at.f] = x;
-      for (int u = 0; u < nf; ++u)
-        fu[at.nf + u] = make_int2((t << 16) | min(ix.fpart, run - u * ix.fpart), at.c + u * ix.fpart);
+      if (base_s) base_s[t] += at.c;  // written above by another group: the scan's barriers lie between
+      else ix.off[x] = at.c;
+      if (tables) {
+        ix.uoff[(int64_t)bg * (gm.T + 1) + t] = at.nu;
+        for (int u = 0; u < nu; ++u)
+          un[at.nu + u] =
+              make_int4(x, min(ix.unit_tokens, run - u * ix.unit_tokens), at.c + u * ix.unit_tokens, nu == 1 ? 1 : 0);
+        if (v.f) ix.fin[(int64_t)bg * gm.T + at.f] = x;
+        for (int u = 0; u < nf; ++u)
+          fu[at.nf + u] = make_int2((t << 16) | min(ix.fpart, run - u * ix.fpart), at.c + u * ix.fpart);
+      }
     }
     carry.add(tot);
   }
-  if (tid == 0) {
+  if (tid == 0 && tables) {
     ix.uoff[(int64_t)bg * (gm.T + 1) + gm.T] = carry.nu;
     ix.ucnt[bg] = carry.nu;
     ix.nfin[bg] = carry.f;
     ix.fcnt[bg] = carry.nf;
+  }
+}
+
+__global__ __launch_bounds__(kScanThreads) void index_scan_kernel(Geom gm, IndexWs ix, int tp) {
+  scan_lists(gm, ix, blockIdx.x, tp, 0, nullptr);
+}
+
+// ---- selections whose blocks are the index's own (64-token blocks without a
+// band, float32): kScanThreads threads per 256-row tile take the tile's (row,
+// slot) pairs, each pair on its own.  A row's entries are the valid prefix of
+// its sel row; bad_s[r] is the first slot past it.  (One thread per row walking
+// its slots took 12 + 20 us for count and fill at 8k tokens and 49 + 85 at 4 x 32k,
+// against 8.5 + 13.7 and 31 + 76; events.)
+
+// The row of pair x (x / ks, by the reciprocal inv = ceil(2^32 / ks); x < 2^14).
+__device__ __forceinline__ int pair_row(int x, int ks, uint32_t inv) { return ks == 1 ? x : (int)__umulhi((uint32_t)x, inv); }
+
+// Stages the tile's sel rows, finds bad_s and sets the tile's bitmap bm [8][T].
+__device__ __forceinline__ void pair_bitmap(uint32_t *bm, int32_t *rows_s, int *bad_s, const int32_t *__restrict__ sel,
+                                            const Geom &gm, int ks, uint32_t inv, int bg, int w) {
+  const int tid = threadIdx.x, msh = __builtin_ctz((unsigned)gm.m);
+  const int nrow = min(kIndexTile, gm.Lq - w * kIndexTile), n = nrow * ks;
+  const int32_t *src = sel + ((int64_t)bg * gm.Lq + (int64_t)w * kIndexTile) * ks;
+  for (int x = tid; x < gm.T * 8; x += kScanThreads) bm[x] = 0u;
+  if (tid < kIndexTile) bad_s[tid] = ks;
+  __syncthreads();
+  for (int x = tid; x < n; x += kScanThreads) {
+    const int r = pair_row(x, ks, inv), t = src[x];
+    rows_s[x] = t;
+    if (!slot_valid(t, (gm.q_pos0 + w * kIndexTile + r) >> msh, gm.T)) atomicMin(&bad_s[r], x - r * ks);
+  }
+  __syncthreads();
+  for (int x = tid; x < n; x += kScanThreads) {
+    const int r = pair_row(x, ks, inv);
+    if (x - r * ks < bad_s[r]) atomicOr(&bm[(r >> 5) * gm.T + rows_s[x]], 1u << (r & 31));
+  }
+  __syncthreads();
+}
+
+__global__ __launch_bounds__(kScanThreads) void index_count_pairs_kernel(const int32_t *__restrict__ sel, Geom gm,
+                                                                         IndexWs ix, uint32_t inv) {
+  extern __shared__ uint32_t bm[];
+  __shared__ int bad_s[kIndexTile];
+  const int w = blockIdx.x, bg = blockIdx.y;
+  pair_bitmap(bm, reinterpret_cast<int32_t *>(bm + 8 * gm.T), bad_s, sel, gm, gm.ksel, inv, bg, w);
+  int32_t *dst = ix.cntw + ((int64_t)bg * ix.W + w) * gm.T;
+  for (int t = threadIdx.x; t < gm.T; t += kScanThreads) {
+    int c = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) c += __popc(bm[k * gm.T + t]);
+    dst[t] = c;
+  }
+}
+
+// SCAN: every workgroup sums the tile counts itself instead of reading a scan
+// kernel's prefixes (one launch less; launch_build_index has the rule).
+template <bool SCAN>
+__global__ __launch_bounds__(kScanThreads) void index_fill_pairs_kernel(const int32_t *__restrict__ sel, Geom gm,
+                                                                        IndexWs ix, uint32_t inv, int tp) {
+  extern __shared__ uint32_t bm[];
+  __shared__ int bad_s[kIndexTile];
+  uint64_t *pre_s = reinterpret_cast<uint64_t *>(bm + 8 * gm.T);
+  int32_t *base_s = reinterpret_cast<int32_t *>(pre_s + gm.T);
+  int32_t *rows_s = base_s + gm.T;
+  // neighbouring tiles write adjacent runs of the same lists: one XCD takes a
+  // contiguous range of (bg, w), so a list's cache lines go through one L2
+  const int logical = xcd_item(blockIdx.x + blockIdx.y * gridDim.x, gridDim.x * gridDim.y);
+  const int w = logical % gridDim.x, bg = logical / gridDim.x, tid = threadIdx.x, ks = gm.ksel;
+  if (SCAN) {
+    scan_lists(gm, ix, bg, tp, w, base_s);
+  } else {
+    const int32_t *tile_off = ix.toff + ((int64_t)bg * ix.W + w) * gm.T;
+    const int32_t *list_off = ix.off + (int64_t)bg * gm.T;
+    for (int t = tid; t < gm.T; t += kScanThreads) base_s[t] = list_off[t] + tile_off[t];
+  }
+  pair_bitmap(bm, rows_s, bad_s, sel, gm, ks, inv, bg, w);  // its barriers also publish base_s
+  for (int t = tid; t < gm.T; t += kScanThreads) {
+    uint64_t pre = 0;
+    int run = 0;  // at most 7 x 32 = 224 rows below the last word
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      pre |= (uint64_t)run << (8 * k);
+      run += __popc(bm[k * gm.T + t]);
+    }
+    pre_s[t] = pre;
+  }
+  __syncthreads();
+  const int n = min(kIndexTile, gm.Lq - w * kIndexTile) * ks;
+  int32_t *pm = ix.pmap + ((int64_t)bg * gm.Lq + (int64_t)w * kIndexTile) * ks;
+  for (int x = tid; x < n; x += kScanThreads) {
+    const int r = pair_row(x, ks, inv), s = x - r * ks;
+    int p = -1;
+    if (s < bad_s[r]) {
+      const int t = rows_s[x], word = r >> 5;
+      // lower rows of the tile that chose t: those of the lower words (a byte of pre_s) and of its own
+      const uint32_t lower = reinterpret_cast<const uint8_t *>(&pre_s[t])[word];
+      p = base_s[t] + (int)lower + __popc(bm[word * gm.T + t] & ((1u << (r & 31)) - 1u));
+      ix.tok[p] = ((w * kIndexTile + r) << 10) | (15 << 6) | s;
+    }
+    pm[x] = p;
   }
 }
 
@@ -465,21 +576,48 @@ hipError_t launch_build_index(const Geom &g, const int32_t *sel, const IndexWs &
   // Each launch's status is taken right after it: the attention kernels gather
   // through these lists, so a failed pass must stop the chain before them.
   hipError_t e;
+  int tp = 64;
+  while (tp < g.T && tp < kScanThreads) tp *= 2;
+  const dim3 tiles(ix.W, g.B * g.Hkv);
+  if (g.sm == g.m && !g.band) {  // (row, slot) pairs
+    const uint32_t inv = (uint32_t)(((1ull << 32) + g.ksel - 1) / g.ksel);  // pair_row
+    const size_t lds = (size_t)g.T * 8 * sizeof(uint32_t) + (size_t)kIndexTile * g.ksel * sizeof(int32_t);
+    const size_t lds_fill = lds + (size_t)g.T * (sizeof(int32_t) + sizeof(uint64_t));
+    // The fill's workgroups sum the counts themselves while there are few: at 32 x
+    // 128 (8k tokens) scan + fill take 10.7 + 13.7 us as two launches and 19 as
+    // one, at 64 x 256 (16k) 11.8 + 16.5 against 25.6, at 128 x 512 with 32 bg (4 x
+    // 32k) 20 + 76 against 206.
+    const bool scan = (int64_t)ix.W * g.T <= 16384;
+    timing_begin("phsa_index_count", s);
+    hipLaunchKernelGGL(index_count_pairs_kernel, tiles, dim3(kScanThreads), lds, s, sel, g, ix, inv);
+    timing_end(s);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (!scan) {
+      timing_begin("phsa_index_scan", s);
+      hipLaunchKernelGGL(index_scan_kernel, dim3(g.B * g.Hkv), dim3(kScanThreads), 0, s, g, ix, tp);
+      timing_end(s);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    timing_begin("phsa_index_fill", s);
+    if (scan)
+      hipLaunchKernelGGL(index_fill_pairs_kernel<true>, tiles, dim3(kScanThreads), lds_fill, s, sel, g, ix, inv, tp);
+    else
+      hipLaunchKernelGGL(index_fill_pairs_kernel<false>, tiles, dim3(kScanThreads), lds_fill, s, sel, g, ix, inv, tp);
+    timing_end(s);
+    return hipGetLastError();
+  }
   const size_t lds = index_lds_bytes(g);
   timing_begin("phsa_index_count", s);
-  hipLaunchKernelGGL(index_count_kernel, dim3(ix.W, g.B * g.Hkv), dim3(256), lds, s, sel, g, ix);
+  hipLaunchKernelGGL(index_count_kernel, tiles, dim3(256), lds, s, sel, g, ix);
   timing_end(s);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   timing_begin("phsa_index_scan", s);
-  int tp = 64;
-  while (tp < g.T && tp < kScanThreads) tp *= 2;
   hipLaunchKernelGGL(index_scan_kernel, dim3(g.B * g.Hkv), dim3(kScanThreads), 0, s, g, ix, tp);
   timing_end(s);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   timing_begin("phsa_index_fill", s);
-  hipLaunchKernelGGL(index_fill_kernel, dim3(ix.W, g.B * g.Hkv), dim3(256),
-                     lds + (size_t)g.T * (sizeof(int32_t) + sizeof(uint64_t)), s, sel,
-                     g, ix);
+  hipLaunchKernelGGL(index_fill_kernel, tiles, dim3(256), lds + (size_t)g.T * (sizeof(int32_t) + sizeof(uint64_t)), s,
+                     sel, g, ix);
   timing_end(s);
   return hipGetLastError();
 }

@@ -10,8 +10,8 @@ from tests.test_gpu_parity import run_full
 pytestmark = pytest.mark.gpu
 
 
-def wl(name, Lq, Lk, Hq, Hkv, d, top_k):
-    return Workload(name, 1, Lq, Lk, Hq, Hkv, d, 64, top_k, 1, 0, "bf16")
+def wl(name, Lq, Lk, Hq, Hkv, d, top_k, n_init=1):
+    return Workload(name, 1, Lq, Lk, Hq, Hkv, d, 64, top_k, n_init, 0, "bf16")
 
 
 # Block 0 is on every row's list, so its list has Lq entries; small problems have
@@ -22,6 +22,9 @@ def wl(name, Lq, Lk, Hq, Hkv, d, top_k):
     wl("unit_g1_more", 129, 1024, 1, 1, 128, 2),
     wl("unit_g8", 17, 512, 8, 1, 64, 3),
     wl("unit_g4_many", 1537, 1600, 8, 2, 64, 5),
+    wl("one_slot", 300, 320, 2, 1, 64, 0, n_init=0),  # Ksel = 1
+    wl("tiles_33", 8300, 8320, 1, 1, 64, 3),          # 33 index tiles: the fill sums two batches of counts per block
+    wl("tiles_65", 16500, 16512, 1, 1, 64, 3),        # 65 x 258 counts: the scan kernel
     wl("blocks_1030", 130, 1030 * 64, 2, 1, 64, 6),   # 1030 blocks: three rounds of the 512-thread scan
 ], ids=lambda c: c.name)
 def test_units_match_oracle(case):
