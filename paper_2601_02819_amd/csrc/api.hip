@@ -55,7 +55,6 @@ size_t index_layout(const Geom &g, char *base, IndexWs *ix) {
   };
   w.cntw = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * R * w.W * g.T));
   w.toff = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * R * w.W * g.T));
-  w.cnt = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * nbgt));
   w.off = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * nbgt));
   w.uoff = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * (nbgt + R)));
   w.ucnt = reinterpret_cast<int32_t *>(take(sizeof(int32_t) * R));
@@ -445,6 +444,7 @@ phsa_status phsa_forward(const phsa_params *p, const void *Q, const void *K, con
     if (!Q || !K || !V || !punct || !K_comp || !sel || !O || !LSE) return PHSA_ERR_NULL;
     if ((st = check_ws(g, PHSA_OP_FORWARD, ws, ws_bytes)) != PHSA_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (g.dtype == PHSA_BF16) g.split = ws;  // bf16 hi/lo of K_comp straight from the compression
     hipError_t e = launch_compress(g, K, punct, K_comp, s);
     if (e == hipSuccess) e = launch_select(g, Q, K_comp, sel, ws, s);
     if (e != hipSuccess) return PHSA_ERR_HIP;

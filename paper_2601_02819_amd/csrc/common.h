@@ -250,4 +250,34 @@ __device__ __forceinline__ bf16x8 pack_bf16x8(const f32x4 &a, const f32x4 &b) {
   return __builtin_convertvector(c, bf16x8);
 }
 
+// Eight consecutive features v of one representative (feature 8 (x mod D / 8) of
+// representative x / (D / 8)) split into bf16 hi + lo (hi + lo = v to about 2^-17
+// relative), with the Euclidean norms of the representative's parts; D / 8
+// consecutive lanes hold one representative and all call this (ok: store).
+template <int D>
+__device__ __forceinline__ void split_row8(const float (&v)[8], int64_t x, bool ok, bf16_t *Mh, bf16_t *Ml,
+                                           float2 *Mnorm) {
+  constexpr int TPR = D / 8;
+  bf16_t hi[8], lo[8];
+  float sh = 0.f, sl = 0.f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    hi[e] = f32_to_bf16(v[e]);
+    const float h = bf16_to_f32(hi[e]);
+    lo[e] = f32_to_bf16(v[e] - h);
+    const float l = bf16_to_f32(lo[e]);
+    sh = fmaf(h, h, sh);
+    sl = fmaf(l, l, sl);
+  }
+#pragma unroll
+  for (int o = 1; o < TPR; o <<= 1) {
+    sh += __shfl_xor(sh, o, 64);
+    sl += __shfl_xor(sl, o, 64);
+  }
+  if (!ok) return;
+  reinterpret_cast<uint4 *>(Mh)[x] = *reinterpret_cast<const uint4 *>(hi);
+  reinterpret_cast<uint4 *>(Ml)[x] = *reinterpret_cast<const uint4 *>(lo);
+  if (x % TPR == 0) Mnorm[x / TPR] = make_float2(sqrtf(sh), sqrtf(sl));
+}
+
 }  // namespace phsa

@@ -7,7 +7,9 @@
 // per-head kernel takes one workgroup per (t, g, b): the block's m rows of d
 // elements are read with 16-byte loads, d / VEC threads cover a row, the 256
 // threads cover 256 * VEC / d rows at a time, and the per-thread float32 partial
-// sums meet in LDS.
+// sums meet in LDS.  With `split` (bf16, phsa_forward) they also leave the bf16
+// hi/lo parts and their norms that the selection scores with, which saves its
+// own pass over K_comp (a launch: 4 us of a 60 us prefill at 1k tokens).
 #include "common.h"
 #include "launch.h"
 
@@ -16,7 +18,7 @@ namespace phsa {
 template <typename T, int D>
 __global__ __launch_bounds__(256) void compress_kernel(const T *__restrict__ K, const uint8_t *__restrict__ punct,
                                                        float *__restrict__ Kc, int Lk, int Hkv, int m, int T_blocks,
-                                                       float lambda) {
+                                                       float lambda, bf16_t *__restrict__ split, int64_t nsplit) {
   constexpr int VEC = 16 / sizeof(T);
   constexpr int TPR = D / VEC;          // threads per key row
   constexpr int NG = 256 / TPR;         // rows in flight
@@ -68,6 +70,16 @@ __global__ __launch_bounds__(256) void compress_kernel(const T *__restrict__ K, 
     const float M0 = a / (float)m;
     const float M = np > 0 ? lambda * M0 + (1.f - lambda) * (p / (float)np) : M0;
     Kc[(((int64_t)b * Hkv + g) * T_blocks + t) * D + c] = M;
+    if (split) red_all[0][c] = M;  // each thread sums its own column
+  }
+  if (!split) return;
+  __syncthreads();
+  if (tid < D / 8) {
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = red_all[0][tid * 8 + e];
+    split_row8<D>(v, (((int64_t)b * Hkv + g) * T_blocks + t) * (D / 8) + tid, true, split, split + nsplit,
+                  reinterpret_cast<float2 *>(split + 2 * nsplit));
   }
 }
 
@@ -81,7 +93,8 @@ __global__ __launch_bounds__(256) void compress_kernel(const T *__restrict__ K, 
 template <typename T, int CV>
 __global__ __launch_bounds__(256) void compress_rows_kernel(const T *__restrict__ K, const uint8_t *__restrict__ punct,
                                                             float *__restrict__ Kc, int Lk, int Hkv, int D, int m,
-                                                            int T_blocks, float lambda) {
+                                                            int T_blocks, float lambda, bf16_t *__restrict__ split,
+                                                            int64_t nsplit) {
   constexpr int VEC = 16 / sizeof(T);
   constexpr int RG = CV >= 256 ? 1 : 256 / CV;  // blocks per workgroup
   constexpr int CPT = CV >= 256 ? CV / 256 : 1;  // vectors per thread
@@ -142,6 +155,15 @@ __global__ __launch_bounds__(256) void compress_rows_kernel(const T *__restrict_
     float *dst = Kc + (((int64_t)b * Hkv + g) * T_blocks + t) * D + f;
 #pragma unroll
     for (int v = 0; v < VEC; v += 4) *reinterpret_cast<float4 *>(dst + v) = make_float4(M[v], M[v + 1], M[v + 2], M[v + 3]);
+    if constexpr (VEC == 8) {
+      if (split) {
+        const int64_t x = ((((int64_t)b * Hkv + g) * T_blocks + t) * D + f) / 8;
+        bf16_t *lo = split + nsplit;
+        float2 *norm = reinterpret_cast<float2 *>(lo + nsplit);
+        if (D == 128) split_row8<128>(M, x, true, split, lo, norm);
+        else split_row8<64>(M, x, true, split, lo, norm);
+      }
+    }
   }
 }
 
@@ -149,6 +171,8 @@ template <typename T, int D>
 static hipError_t launch_compress_t(const Geom &g, const void *K, const uint8_t *punct, float *Kc, hipStream_t s) {
   timing_begin("phsa_compress", s);
   const int cv = g.Hkv * D * (int)sizeof(T) / 16;  // 16-byte vectors per token row
+  bf16_t *split = static_cast<bf16_t *>(g.split);
+  const int64_t ns = (int64_t)g.B * g.Hkv * g.T * D;
   // short blocks: the per-head kernel's workgroups would carry m * D elements
   // each (4 KB at m = 16), too little to hide a launch; at m >= 64 the two run
   // at the same rate (the per-head kernel slightly ahead)
@@ -158,20 +182,20 @@ static hipError_t launch_compress_t(const Geom &g, const void *K, const uint8_t 
     const T *Kt = static_cast<const T *>(K);
     if (cv == 64)
       hipLaunchKernelGGL((compress_rows_kernel<T, 64>), grid, dim3(256), 0, s, Kt, punct, Kc, g.Lk, g.Hkv, D, g.m, g.T,
-                         g.lambda);
+                         g.lambda, split, ns);
     else if (cv == 128)
       hipLaunchKernelGGL((compress_rows_kernel<T, 128>), grid, dim3(256), 0, s, Kt, punct, Kc, g.Lk, g.Hkv, D, g.m, g.T,
-                         g.lambda);
+                         g.lambda, split, ns);
     else if (cv == 256)
       hipLaunchKernelGGL((compress_rows_kernel<T, 256>), grid, dim3(256), 0, s, Kt, punct, Kc, g.Lk, g.Hkv, D, g.m, g.T,
-                         g.lambda);
+                         g.lambda, split, ns);
     else
       hipLaunchKernelGGL((compress_rows_kernel<T, 512>), grid, dim3(256), 0, s, Kt, punct, Kc, g.Lk, g.Hkv, D, g.m, g.T,
-                         g.lambda);
+                         g.lambda, split, ns);
   } else {
     const dim3 grid(g.T, g.Hkv, g.B);
     hipLaunchKernelGGL((compress_kernel<T, D>), grid, dim3(256), 0, s, static_cast<const T *>(K), punct, Kc, g.Lk,
-                       g.Hkv, g.m, g.T, g.lambda);
+                       g.Hkv, g.m, g.T, g.lambda, split, ns);
   }
   timing_end(s);
   return hipGetLastError();

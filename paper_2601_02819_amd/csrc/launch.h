@@ -21,6 +21,8 @@ struct Geom {
   int sel_mode;       // group aggregation of block scores: 0 summed logits, 1 summed per-head softmax
   int sm;             // block size of the selection (m of a tile geometry is 64; n_init, window keep sm units)
   int band;           // 1: the local window of every row holding it whole is attended by the band kernels
+  void *split;        // phsa_forward: the selection's scratch (select_split_bytes), which the compression
+                      // fills beside K_comp so that the selection need not; NULL elsewhere
 };
 
 // Index (inverted selection) workspace, carved out of the caller's buffer.
@@ -35,7 +37,6 @@ struct IndexWs {
   int64_t nnz_max;    // upper bound on list entries
   int32_t *cntw;      // [R, W, T]      per-tile counts
   int32_t *toff;      // [R, W, T]      exclusive prefix of cntw over the tiles
-  int32_t *cnt;       // [R * T]        list length per (b, g, t)
   int32_t *off;       // [R * T]        list start per (b, g, t)
   int32_t *uoff;      // [R, T + 1]     first backward unit of (b, g, t) within its (b, g)'s
   int32_t *ucnt;      // [R]            backward units of (b, g)

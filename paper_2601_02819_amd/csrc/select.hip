@@ -753,7 +753,6 @@ template <int D>
 __global__ __launch_bounds__(256) void select_split_kernel(const float *__restrict__ Kc, bf16_t *__restrict__ Mh,
                                                            bf16_t *__restrict__ Ml, float2 *__restrict__ Mnorm,
                                                            int64_t n8) {
-  constexpr int TPR = D / 8;
   const int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x;
   float v[8];
   if (x < n8) {
@@ -764,26 +763,7 @@ __global__ __launch_bounds__(256) void select_split_kernel(const float *__restri
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = 0.f;
   }
-  bf16_t hi[8], lo[8];
-  float sh = 0.f, sl = 0.f;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    hi[e] = f32_to_bf16(v[e]);
-    const float h = bf16_to_f32(hi[e]);
-    lo[e] = f32_to_bf16(v[e] - h);
-    const float l = bf16_to_f32(lo[e]);
-    sh = fmaf(h, h, sh);
-    sl = fmaf(l, l, sl);
-  }
-#pragma unroll
-  for (int o = 1; o < TPR; o <<= 1) {
-    sh += __shfl_xor(sh, o, 64);
-    sl += __shfl_xor(sl, o, 64);
-  }
-  if (x >= n8) return;
-  reinterpret_cast<uint4 *>(Mh)[x] = *reinterpret_cast<const uint4 *>(hi);
-  reinterpret_cast<uint4 *>(Ml)[x] = *reinterpret_cast<const uint4 *>(lo);
-  if (x % TPR == 0) Mnorm[x / TPR] = make_float2(sqrtf(sh), sqrtf(sl));
+  split_row8<D>(v, x, x < n8, Mh, Ml, Mnorm);
 }
 
 // The value of lane (l16 + r) % 16 of this lane's 16-lane row (DPP row_ror:r).
@@ -1331,10 +1311,12 @@ static hipError_t launch_select_mfma(const Geom &g, const void *Q, const float *
   const int64_t n = (int64_t)g.B * g.Hkv * g.T * D;
   bf16_t *mh = reinterpret_cast<bf16_t *>(ws), *ml = mh + n;
   float2 *mnorm = reinterpret_cast<float2 *>(ml + n);
-  timing_begin("phsa_select_split", s);
-  hipLaunchKernelGGL(select_split_kernel<D>, dim3((unsigned)((n / 8 + 255) / 256)), dim3(256), 0, s, Kc, mh, ml, mnorm,
-                     n / 8);
-  timing_end(s);
+  if (!g.split) {  // the compression has not filled the scratch
+    timing_begin("phsa_select_split", s);
+    hipLaunchKernelGGL(select_split_kernel<D>, dim3((unsigned)((n / 8 + 255) / 256)), dim3(256), 0, s, Kc, mh, ml, mnorm,
+                       n / 8);
+    timing_end(s);
+  }
   timing_begin("phsa_select", s);
   // With fewer than the 512 workgroups of 128 rows that the chip holds at once,
   // a workgroup's own chain (bar, appends and final rank of each wave's rows) is
@@ -1378,10 +1360,12 @@ static hipError_t launch_select_softmax_mfma(const Geom &g, const void *Q, const
   const int64_t n = (int64_t)g.B * g.Hkv * g.T * D;
   bf16_t *mh = reinterpret_cast<bf16_t *>(ws), *ml = mh + n;
   float2 *mnorm = reinterpret_cast<float2 *>(ml + n);
-  timing_begin("phsa_select_split", s);
-  hipLaunchKernelGGL(select_split_kernel<D>, dim3((unsigned)((n / 8 + 255) / 256)), dim3(256), 0, s, Kc, mh, ml, mnorm,
-                     n / 8);
-  timing_end(s);
+  if (!g.split) {  // the compression has not filled the scratch
+    timing_begin("phsa_select_split", s);
+    hipLaunchKernelGGL(select_split_kernel<D>, dim3((unsigned)((n / 8 + 255) / 256)), dim3(256), 0, s, Kc, mh, ml, mnorm,
+                       n / 8);
+    timing_end(s);
+  }
   constexpr int NTOK = 64 / G;
   const dim3 grid((g.Lq + NTOK - 1) / NTOK, g.B * g.Hkv);
   timing_begin("phsa_select_softmax", s);
