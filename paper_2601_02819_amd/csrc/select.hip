@@ -375,56 +375,85 @@ __global__ __launch_bounds__(256) void select_softmax_kernel(const T *__restrict
   finish_rows<KMAX>(ls, lt, smem, picks, wave == 0 && row_ok && hh == 0, i, cur, bg, sel, gm);
 }
 
+// A candidate list entry is (score, (q4 << 16) | (0xffff - block)): q4 names
+// the entry's row among the four rows that share the list.  For ranking, an
+// entry becomes a 64-bit key: the score's float32 bits mapped to an
+// order-preserving unsigned integer in the high word (-0 counted as +0), the
+// same low word.  For two entries of one row the key order is the selection's
+// order (score descending, then block ascending), so a rank is one 64-bit
+// compare.
+__device__ __forceinline__ uint64_t cand_key(float2 e) {
+  const uint32_t b = __float_as_uint(e.x + 0.f);
+  const uint32_t hi = (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+  return ((uint64_t)hi << 32) | __float_as_uint(e.y);
+}
+__device__ __forceinline__ float2 key_entry(uint64_t key) {
+  const uint32_t hi = (uint32_t)(key >> 32);
+  return make_float2(__uint_as_float((hi & 0x80000000u) ? (hi & 0x7fffffffu) : ~hi), __uint_as_float((uint32_t)key));
+}
+__device__ __forceinline__ int key_row(uint64_t key) { return ((uint32_t)key >> 16) & 3; }
+__device__ __forceinline__ int key_block(uint64_t key) { return 0xffff - ((uint32_t)key & 0xffff); }
+
 // Softmax-sum selection on the matrix cores (bf16 inputs; mode of
-// select_softmax_kernel).  A workgroup holds 64 (query token, head) pairs,
-// 64 / G tokens with their heads inner; wave w owns pairs 16w..16w+15 as one
-// 16-row MFMA tile.  A pair's query is scaled to log2 units and split into
+// select_softmax_kernel).  A workgroup holds 64 RT (query token, head) pairs,
+// 64 RT / G tokens with their heads inner; wave w owns RT 16-row MFMA tiles of
+// pairs, which share every representative fragment read from LDS.  A
+// pair's query is scaled to log2 units and split into
 // bf16 hi + lo like the representatives (select_split_kernel), and the three
 // chains hi.hi + hi.lo + lo.hi give its logits to about 2^-17 relative.  In
-// the accumulator layout lane (q4, l16) holds pairs 4 q4 + r of its tile for
+// the accumulator layout lane (q4, l16) holds pairs 4 q4 + r of a tile for
 // blocks t0 + 16 nt + l16: the G heads of a token sit in the same lane (G <= 4)
 // or in lanes q4 and q4 ^ 1 (G = 8), so a token's group score
 // log2 sum_h 2^(x_h - lse_h) is formed without LDS, and the 16 lanes of a
 // quarter-wave see all blocks of their tokens, each a fixed residue mod 16.
 //   pass 1: the complete causal blocks t < cur: a running (max, sum) of 2^x per
 //           lane and pair, merged over the 16 lanes: the log2 normaliser lse.
-//   pass 2: the candidates' group scores; each lane keeps the best two of its
-//           stripe per token.  A token's 32 stripe tops are 32 distinct
-//           blocks, so the largest v with at least k of them >= v (the bar)
-//           lies at or below the token's k-th best score.
-//   pass 3: the group scores again; those >= bar are appended to the token's
-//           LDS list (slots from an LDS counter: about k + 3 per token on
-//           random inputs).  A list that could overflow with the next chunk
+//   pass 2: lower bounds of the candidates' group scores; each lane keeps the
+//           best two of its stripe per token.  A token's 32 stripe tops are 32
+//           distinct blocks, so the largest v with at least k of them >= v (the
+//           bar) lies at or below the token's k-th best score.  The bounds come
+//           from the hi.hi chain alone, each pair's logit lowered by the margin
+//           of select_mfma_kernel (the group score rises with every logit): a
+//           third of the products, half of the reads, a few more candidates.
+//   pass 3: the exact group scores; those >= bar are appended to the token's
+//           LDS list (a few more than k per token on random inputs).  A list that could overflow with the next chunk
 //           (many equal scores) is cut to its k best first.
 //   final:  the k best of each list (score descending, block ascending) by
 //           counting ranks, so the order of arrival does not matter.
-// Scores of passes 2 and 3 come from identical instruction sequences on the
-// same data, so they are bitwise equal and the bar never drops a winner.
-template <int D, int G, int KMAX>
-__global__ __launch_bounds__(256) void select_softmax_mfma_kernel(const bf16_t *__restrict__ Q,
-                                                                  const bf16_t *__restrict__ Mh_g,
-                                                                  const bf16_t *__restrict__ Ml_g,
-                                                                  int32_t *__restrict__ sel, Geom gm) {
+// What bounds it: LDS reads of the fragments and the transcendentals of the
+// group scores, and the waits for each chunk.  At 16k tokens (T = 256, 16/8 heads) 156 us; 230 with one
+// row tile per wave, three chains in pass 2, chunks staged through registers, LDS
+// counters for the appends and one thread sorting each row.
+template <int D, int G, int KMAX, int RT>
+__global__ __launch_bounds__(256, (KMAX > 16 && G == 1 ? 1 : 2)) void select_softmax_mfma_kernel(const bf16_t *__restrict__ Q,
+                                                                     const bf16_t *__restrict__ Mh_g,
+                                                                     const bf16_t *__restrict__ Ml_g,
+                                                                     const float2 *__restrict__ Mnorm_g,
+                                                                     int32_t *__restrict__ sel, Geom gm) {
   constexpr int CH = 64;
-  constexpr int NTOK = 64 / G;            // tokens per workgroup
+  constexpr int NTOK = 64 * RT / G;       // tokens per workgroup
   constexpr int GL = G < 4 ? G : 4;       // heads of a token within one lane
-  constexpr int TPL = 4 / GL;             // tokens per lane (lanes q4 even only when G = 8)
+  constexpr int TPL = 4 / GL;             // tokens per lane and tile (lanes q4 even only when G = 8)
   constexpr int LPT = 256 / NTOK;         // threads per token when ranking
   constexpr int CAP = KMAX + CH;          // list slots per token: k best + one chunk
-  constexpr int MP = D + 16;              // 16-byte fragment reads of 16 rows are conflict-free
+  constexpr int TP = 36;                  // pitch of a token's 32 stripe tops (bank spread)
   constexpr int KB = D / 32;
-  constexpr int NL = CH * D / (256 * 8);
-  constexpr int BUF = 2 * CH * MP * 2;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[BUF];
-  __shared__ float2 cand[NTOK][CAP];      // (score, block as int bits), unordered
+  constexpr int TD = CH * D;              // elements of a staged chunk (hi or lo), swizzled
+  constexpr int VPR = D / 8, RPI = 64 / VPR, NI = CH / RPI / 4;  // copies per wave per chunk
+  static_assert(LPT >= 1 && NTOK * TP * 4 <= 2 * TD * 2 && NTOK * KMAX * 8 <= 2 * TD * 2, "scratch in the staging area");
+  __shared__ __attribute__((aligned(16))) bf16_t stg[2 * TD];
+  // odd pitches: the tokens a wave reads together lie in different banks
+  __shared__ uint64_t cand[NTOK][CAP + 1];  // cand_key of (score, 0xffff - block): a larger key is the better block
   __shared__ int ccnt[NTOK];
-  __shared__ int picks[NTOK][KMAX];
+  __shared__ int picks[NTOK][KMAX + 1];
   __shared__ float bar_s[NTOK];
-  bf16_t *Mh = reinterpret_cast<bf16_t *>(smem);
-  bf16_t *Ml = Mh + CH * MP;
-  float *tops = reinterpret_cast<float *>(smem);   // bar and cuts: [NTOK][32] / [NTOK][2 KMAX]
+  __shared__ float2 nmax_s[4];
+  __shared__ int full_s;                  // some list could overflow with another chunk
+  bf16_t *Mh = stg, *Ml = stg + TD;
+  float *tops = reinterpret_cast<float *>(stg);             // bar: [NTOK][TP]
+  uint64_t *best_k = reinterpret_cast<uint64_t *>(stg);     // cuts: [NTOK][KMAX]
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, q4 = lane >> 4, kq = q4 * 8;
   const TileOrder wo;
   const int bg = wo.bg, b = bg / gm.Hkv, g = bg % gm.Hkv;
@@ -433,268 +462,368 @@ __global__ __launch_bounds__(256) void select_softmax_mfma_kernel(const bf16_t *
   const int cur_max = (gm.q_pos0 + last_i) / gm.m;
   const int t_end = max(0, cur_max - gm.window / gm.m);
   const int k = gm.top_k;
+  auto pair0 = [&](int j) { return (wave * RT + j) * 16; };  // first pair of tile j of this wave
 
-  // A operand: pair 16 w + l16 (token (16 w + l16) / G, head l16 % G)
-  bf16x8 ah[KB], al[KB];
-  {
-    const float f = gm.scale * kLog2e;
-    const int p = wave * 16 + l16;
-    const int i = min(i0 + p / G, gm.Lq - 1);
+  u32x4 qraw[RT][KB];  // in flight while the norms are read
+#pragma unroll
+  for (int j = 0; j < RT; ++j) {
+    const int p = pair0(j) + l16, i = min(i0 + p / G, gm.Lq - 1);
     const bf16_t *src = Q + (((int64_t)b * gm.Lq + i) * gm.Hq + g * G + p % G) * D;
 #pragma unroll
+    for (int kb = 0; kb < KB; ++kb) qraw[j][kb] = *reinterpret_cast<const u32x4 *>(src + kb * 32 + kq);
+  }
+  // largest |M_hi| and |M_lo| over the (b, g)'s blocks, for the pass-2 margin
+  {
+    const float2 *mn_bg = Mnorm_g + (int64_t)bg * gm.T;
+    float2 mx = make_float2(0.f, 0.f);
+    for (int t = tid; t < gm.T; t += 256) {
+      const float2 v = mn_bg[t];
+      mx.x = fmaxf(mx.x, v.x);
+      mx.y = fmaxf(mx.y, v.y);
+    }
+    mx.x = wave_max(mx.x);
+    mx.y = wave_max(mx.y);
+    if (lane == 0) nmax_s[wave] = mx;
+  }
+  // A operands: pair pair0(j) + l16 (token pair / G, head pair % G), and the norms of the query's parts
+  bf16x8 ah[RT][KB], al[RT][KB];
+  float qnh[RT], qnl[RT];
+#pragma unroll
+  for (int j = 0; j < RT; ++j) {
+    const float f = gm.scale * kLog2e;
+    float sh = 0.f, sl = 0.f;
+#pragma unroll
     for (int kb = 0; kb < KB; ++kb) {
-      const uint4 raw = *reinterpret_cast<const uint4 *>(src + kb * 32 + kq);
-      const bf16_t *v = reinterpret_cast<const bf16_t *>(&raw);
+      const bf16_t *v = reinterpret_cast<const bf16_t *>(&qraw[j][kb]);
       bf16_t hi[8], lo[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const float x = bf16_to_f32(v[e]) * f;
         hi[e] = f32_to_bf16(x);
-        lo[e] = f32_to_bf16(x - bf16_to_f32(hi[e]));
+        const float h = bf16_to_f32(hi[e]);
+        lo[e] = f32_to_bf16(x - h);
+        const float l = bf16_to_f32(lo[e]);
+        sh = fmaf(h, h, sh);
+        sl = fmaf(l, l, sl);
       }
-      ah[kb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(hi));
-      al[kb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(lo));
+      ah[j][kb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(hi));
+      al[j][kb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(lo));
     }
+    sh += __shfl_xor(sh, 16, 64);
+    sh += __shfl_xor(sh, 32, 64);
+    sl += __shfl_xor(sl, 16, 64);
+    sl += __shfl_xor(sl, 32, 64);
+    qnh[j] = sqrtf(sh);
+    qnl[j] = sqrtf(sl);
   }
-  // accumulator row r of this lane: pair 16 w + 4 q4 + r; its token and bounds
-  const int tok0 = (wave * 16 + q4 * 4) / G;   // first token of this lane's rows
-  int cur_r[4], lo_t[TPL];
+  // accumulator row r of tile j: pair pair0(j) + 4 q4 + r; its token and bounds
+  int tok0[RT], cur_r[RT][4], lo_t[RT][TPL];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int i = i0 + (wave * 16 + q4 * 4 + r) / G;
-    cur_r[r] = i < gm.Lq ? (gm.q_pos0 + i) / gm.m : 0;
-  }
+  for (int j = 0; j < RT; ++j) {
+    tok0[j] = (pair0(j) + q4 * 4) / G;   // first token of this lane's rows
 #pragma unroll
-  for (int u = 0; u < TPL; ++u) {
-    const int i = i0 + tok0 + u;
-    lo_t[u] = i < gm.Lq ? max(0, (gm.q_pos0 + i) / gm.m - gm.window / gm.m) : 0;
+    for (int r = 0; r < 4; ++r) {
+      const int i = i0 + (pair0(j) + q4 * 4 + r) / G;
+      cur_r[j][r] = i < gm.Lq ? (gm.q_pos0 + i) / gm.m : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < TPL; ++u) {
+      const int i = i0 + tok0[j] + u;
+      lo_t[j][u] = i < gm.Lq ? max(0, (gm.q_pos0 + i) / gm.m - gm.window / gm.m) : 0;
+    }
   }
 
   const bf16_t *mh_bg = Mh_g + (int64_t)bg * gm.T * D;
   const bf16_t *ml_bg = Ml_g + (int64_t)bg * gm.T * D;
-  uint4 ph[NL], pl[NL];
-  auto fetch = [&](int t0) {
-    const int nblk = min(CH, gm.T - t0);
+  // blocks t0 .. t0 + 63 straight into a swizzled tile; rows past the last block
+  // repeat it (never complete causal blocks nor candidates)
+  auto copy = [&](const bf16_t *src, int t0, bf16_t *dst) {
 #pragma unroll
-    for (int x = 0; x < NL; ++x) {
-      const int e = (tid + 256 * x) * 8, row = e / D, c = e % D;
-      const int64_t off = (int64_t)(t0 + row) * D + c;
-      ph[x] = row < nblk ? *reinterpret_cast<const uint4 *>(mh_bg + off) : make_uint4(0u, 0u, 0u, 0u);
-      pl[x] = row < nblk ? *reinterpret_cast<const uint4 *>(ml_bg + off) : make_uint4(0u, 0u, 0u, 0u);
+    for (int v = 0; v < NI; ++v) {
+      const int blk = wave * NI + v, r = blk * RPI + lane / VPR, cc = (lane % VPR) ^ (r & (VPR - 1));
+      __builtin_amdgcn_global_load_lds(src + (int64_t)min(t0 + r, gm.T - 1) * D + cc * 8,
+                                       (lds_void_t *)(dst + blk * RPI * D), 16, 0, 0);
     }
   };
-  auto stage = [&]() {
+  auto frag = [&](const bf16_t *tile, int n0, int kb) { return load_bf16x8(&tile[swz<D>(n0 + l16, kb * 32 + kq)]); };
+  // logits of the staged chunk, all three chains or hi.hi alone:
+  // acc[j][nt][r] = x(pair pair0(j) + 4 q4 + r, block t0 + 16 nt + l16)
+  auto scores = [&](f32x4 (&acc)[RT][4], auto exact_c) {
+    constexpr bool EXACT = decltype(exact_c)::value;
 #pragma unroll
-    for (int x = 0; x < NL; ++x) {
-      const int e = (tid + 256 * x) * 8, row = e / D, c = e % D;
-      *reinterpret_cast<uint4 *>(&Mh[row * MP + c]) = ph[x];
-      *reinterpret_cast<uint4 *>(&Ml[row * MP + c]) = pl[x];
-    }
-  };
-  // exact logits of the staged chunk: acc[nt][r] = x(pair 16 w + 4 q4 + r, block t0 + 16 nt + l16)
-  auto scores = [&](f32x4 (&acc)[4]) {
+    for (int j = 0; j < RT; ++j)
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int nt = 0; nt < 4; ++nt) acc[j][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) {
       bf16x8 bh[4], bl[4];
 #pragma unroll
       for (int nt = 0; nt < 4; ++nt) {
-        bh[nt] = load_bf16x8(&Mh[(nt * 16 + l16) * MP + kb * 32 + kq]);
-        bl[nt] = load_bf16x8(&Ml[(nt * 16 + l16) * MP + kb * 32 + kq]);
+        bh[nt] = frag(Mh, nt * 16, kb);
+        if (EXACT) bl[nt] = frag(Ml, nt * 16, kb);
       }
-      // each chain over the 4 accumulators in turn (consecutive MFMAs independent;
+      // each chain over the accumulators in turn (consecutive MFMAs independent;
       // every accumulator still takes hi.hi, hi.lo, lo.hi of each kb in that order)
 #pragma unroll
-      for (int nt = 0; nt < 4; ++nt) acc[nt] = mfma16x16x32(ah[kb], bh[nt], acc[nt]);
+      for (int nt = 0; nt < 4; ++nt)
 #pragma unroll
-      for (int nt = 0; nt < 4; ++nt) acc[nt] = mfma16x16x32(ah[kb], bl[nt], acc[nt]);
+        for (int j = 0; j < RT; ++j) acc[j][nt] = mfma16x16x32(ah[j][kb], bh[nt], acc[j][nt]);
+      if (EXACT) {
 #pragma unroll
-      for (int nt = 0; nt < 4; ++nt) acc[nt] = mfma16x16x32(al[kb], bh[nt], acc[nt]);
+        for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+          for (int j = 0; j < RT; ++j) acc[j][nt] = mfma16x16x32(ah[j][kb], bl[nt], acc[j][nt]);
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt)
+#pragma unroll
+          for (int j = 0; j < RT; ++j) acc[j][nt] = mfma16x16x32(al[j][kb], bh[nt], acc[j][nt]);
+      }
     }
   };
-  // one pass over the chunks of [ta, tb): body(t0, acc) after the scores
-  auto sweep = [&](int ta, int tb, auto body) {
-    fetch(ta);
+  // one pass over the chunks of [ta, tb): free() once every wave is done with the
+  // chunk before, body(t0, acc) after the scores
+  auto sweep = [&](int ta, int tb, auto exact_c, auto free, auto body) {
     for (int t0 = ta; t0 < tb; t0 += CH) {
-      __syncthreads();
-      stage();
-      __syncthreads();
-      if (t0 + CH < tb) fetch(t0 + CH);
-      f32x4 acc[4];
-      scores(acc);
+      lds_barrier();
+      free();
+      copy(mh_bg, t0, Mh);
+      if (decltype(exact_c)::value) copy(ml_bg, t0, Ml);
+      dma_wait();
+      lds_barrier();
+      f32x4 acc[RT][4];
+      scores(acc, exact_c);
       body(t0, acc);
     }
   };
-  float lse[4];
-  // group score of token u of this lane for block t0 + 16 nt + l16 (all lanes call this)
-  auto group = [&](const f32x4 &a, int u) {
-    float m = a[u * GL] - lse[u * GL];
+  auto nothing = [] {};
+  float lse[RT][4];
+  // group score of token u of tile j for block t0 + 16 nt + l16, the heads' logits less n (all lanes call this)
+  auto group = [&](const f32x4 &a, const float (&n)[4], int u) {
+    float m = a[u * GL] - n[u * GL];
 #pragma unroll
-    for (int r = 1; r < GL; ++r) m = fmaxf(m, a[u * GL + r] - lse[u * GL + r]);
+    for (int r = 1; r < GL; ++r) m = fmaxf(m, a[u * GL + r] - n[u * GL + r]);
     if (G == 8) m = fmaxf(m, __shfl_xor(m, 16, 64));
     float e = 0.f;
+    if (G == 2) {  // the larger head's term is 2^0 = 1
+      e = 1.f + __builtin_amdgcn_exp2f(fminf(a[u * GL] - n[u * GL], a[u * GL + 1] - n[u * GL + 1]) - m);
+    } else {
 #pragma unroll
-    for (int r = 0; r < GL; ++r) e += __builtin_amdgcn_exp2f(a[u * GL + r] - lse[u * GL + r] - m);
+      for (int r = 0; r < GL; ++r) e += __builtin_amdgcn_exp2f(a[u * GL + r] - n[u * GL + r] - m);
+    }
     if (G == 8) e += __shfl_xor(e, 16, 64);
     return m + __builtin_amdgcn_logf(e);   // e in [1, G]
   };
   const bool lane_tok = G < 8 || (q4 & 1) == 0;   // lanes that hold whole tokens
 
   if (tid < NTOK) ccnt[tid] = 0;
+  if (tid == 0) full_s = 0;
   if (k > 0 && t_end > gm.n_init) {
     // ---- pass 1: log2 normaliser of every pair over blocks 0 .. cur - 1
-    float mx[4], sm[4];
+    float mx[RT][4], sm[RT][4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      mx[r] = -INFINITY;
-      sm[r] = 0.f;
-    }
-    sweep(0, cur_max, [&](int t0, f32x4 (&acc)[4]) {
+    for (int j = 0; j < RT; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        float cm = -INFINITY;
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-          if (t0 + nt * 16 + l16 < cur_r[r]) cm = fmaxf(cm, acc[nt][r]);
-        const float nm = fmaxf(mx[r], cm);
-        if (nm == -INFINITY) continue;
-        float add = 0.f;
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-          if (t0 + nt * 16 + l16 < cur_r[r]) add += __builtin_amdgcn_exp2f(acc[nt][r] - nm);
-        sm[r] = sm[r] * __builtin_amdgcn_exp2f(mx[r] - nm) + add;  // 2^-inf = 0 on the first block
-        mx[r] = nm;
+        mx[j][r] = -INFINITY;
+        sm[j][r] = 0.f;
       }
-    });
+    sweep(0, cur_max, std::true_type{}, nothing, [&](int t0, f32x4 (&acc)[RT][4]) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      float m = mx[r], l = sm[r];
+      for (int j = 0; j < RT; ++j)
 #pragma unroll
-      for (int o = 1; o < 16; o <<= 1) {
-        const float om = __shfl_xor(m, o, 64), ol = __shfl_xor(l, o, 64);
-        const float nm = fmaxf(m, om);
-        l = (l > 0.f ? l * __builtin_amdgcn_exp2f(m - nm) : 0.f) + (ol > 0.f ? ol * __builtin_amdgcn_exp2f(om - nm) : 0.f);
-        m = nm;
-      }
-      lse[r] = l > 0.f ? m + __builtin_amdgcn_logf(l) : 0.f;  // cur = 0: no candidate uses it
-    }
-
-    // ---- pass 2: best two group scores of each lane's stripe, per token
-    float top1[TPL], top2[TPL];
+        for (int r = 0; r < 4; ++r) {
+          float cm = -INFINITY;
 #pragma unroll
-    for (int u = 0; u < TPL; ++u) top1[u] = top2[u] = -INFINITY;
-    sweep(gm.n_init, t_end, [&](int t0, f32x4 (&acc)[4]) {
+          for (int nt = 0; nt < 4; ++nt)
+            if (t0 + nt * 16 + l16 < cur_r[j][r]) cm = fmaxf(cm, acc[j][nt][r]);
+          const float nm = fmaxf(mx[j][r], cm);
+          if (nm == -INFINITY) continue;
+          float add = 0.f;
 #pragma unroll
-      for (int nt = 0; nt < 4; ++nt) {
-        const int t = t0 + nt * 16 + l16;
-#pragma unroll
-        for (int u = 0; u < TPL; ++u) {
-          const float sv = group(acc[nt], u);
-          const float v = t < lo_t[u] ? sv : -INFINITY;
-          const bool c1 = v > top1[u], c2 = v > top2[u];
-          top2[u] = c1 ? top1[u] : (c2 ? v : top2[u]);
-          top1[u] = c1 ? v : top1[u];
+          for (int nt = 0; nt < 4; ++nt)
+            if (t0 + nt * 16 + l16 < cur_r[j][r]) add += __builtin_amdgcn_exp2f(acc[j][nt][r] - nm);
+          sm[j][r] = sm[j][r] * __builtin_amdgcn_exp2f(mx[j][r] - nm) + add;  // 2^-inf = 0 on the first block
+          mx[j][r] = nm;
         }
-      }
     });
-    // ---- bar of each token: the largest stripe top v with at least k stripe tops >= v
-    __syncthreads();
+    float low[RT][4];  // lse plus the pair's margin
+    float2 nm2 = nmax_s[0];
 #pragma unroll
-    for (int u = 0; u < TPL; ++u)
-      if (lane_tok) {
-        tops[(tok0 + u) * 32 + 2 * l16] = top1[u];
-        tops[(tok0 + u) * 32 + 2 * l16 + 1] = top2[u];
+    for (int w = 1; w < 4; ++w) {
+      nm2.x = fmaxf(nm2.x, nmax_s[w].x);
+      nm2.y = fmaxf(nm2.y, nmax_s[w].y);
+    }
+#pragma unroll
+    for (int j = 0; j < RT; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        float m = mx[j][r], l = sm[j][r];
+#pragma unroll
+        for (int o = 1; o < 16; o <<= 1) {
+          const float om = __shfl_xor(m, o, 64), ol = __shfl_xor(l, o, 64);
+          const float nm = fmaxf(m, om);
+          l = (l > 0.f ? l * __builtin_amdgcn_exp2f(m - nm) : 0.f) + (ol > 0.f ? ol * __builtin_amdgcn_exp2f(om - nm) : 0.f);
+          m = nm;
+        }
+        lse[j][r] = l > 0.f ? m + __builtin_amdgcn_logf(l) : 0.f;  // cur = 0: no candidate uses it
+        // |x - hi.hi| <= |q_hi| |M_lo| + |q_lo| |M_hi| plus the chains' rounding, below 2^-15 |q_hi| |M_hi|
+        const float eh = __shfl(qnh[j], q4 * 4 + r, 64), el = __shfl(qnl[j], q4 * 4 + r, 64);
+        low[j][r] = lse[j][r] + fmaf(eh, fmaf(nm2.x, 0x1p-15f, nm2.y), el * nm2.x) * 1.0001f;
       }
+
+    // ---- pass 2: best two lower bounds of each lane's stripe, per token
+    float top1[RT][TPL], top2[RT][TPL];
+#pragma unroll
+    for (int j = 0; j < RT; ++j)
+#pragma unroll
+      for (int u = 0; u < TPL; ++u) top1[j][u] = top2[j][u] = -INFINITY;
+    sweep(gm.n_init, t_end, std::false_type{}, nothing, [&](int t0, f32x4 (&acc)[RT][4]) {
+#pragma unroll
+      for (int j = 0; j < RT; ++j)
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) {
+          const int t = t0 + nt * 16 + l16;
+#pragma unroll
+          for (int u = 0; u < TPL; ++u) {
+            const float sv = group(acc[j][nt], low[j], u);
+            const float v = t < lo_t[j][u] ? sv : -INFINITY;
+            top2[j][u] = __builtin_amdgcn_fmed3f(top1[j][u], top2[j][u], v);  // the middle of the three
+            top1[j][u] = fmaxf(top1[j][u], v);
+          }
+        }
+    });
+    // ---- bar of each token: the largest stripe top v with at least k stripe tops
+    // >= v, less the rounding of the two group scores' exponentials and logarithm
+    lds_barrier();
+#pragma unroll
+    for (int j = 0; j < RT; ++j)
+#pragma unroll
+      for (int u = 0; u < TPL; ++u)
+        if (lane_tok) {
+          *reinterpret_cast<float2 *>(&tops[(tok0[j] + u) * TP + 2 * l16]) = make_float2(top1[j][u], top2[j][u]);
+        }
     wave_lds_sync();
 #pragma unroll
-    for (int u = 0; u < TPL; ++u) {
-      const float4 *rowp = reinterpret_cast<const float4 *>(tops + (tok0 + u) * 32);
-      int c1 = 0, c2 = 0;
+    for (int j = 0; j < RT; ++j)
 #pragma unroll
-      for (int x = 0; x < 8; ++x) {
-        const float4 v = rowp[x];
-        c1 += (v.x >= top1[u]) + (v.y >= top1[u]) + (v.z >= top1[u]) + (v.w >= top1[u]);
-        c2 += (v.x >= top2[u]) + (v.y >= top2[u]) + (v.z >= top2[u]) + (v.w >= top2[u]);
+      for (int u = 0; u < TPL; ++u) {
+        const float4 *rowp = reinterpret_cast<const float4 *>(tops + (tok0[j] + u) * TP);
+        int c1 = 0, c2 = 0;
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+          const float4 v = rowp[x];
+          c1 += (v.x >= top1[j][u]) + (v.y >= top1[j][u]) + (v.z >= top1[j][u]) + (v.w >= top1[j][u]);
+          c2 += (v.x >= top2[j][u]) + (v.y >= top2[j][u]) + (v.z >= top2[j][u]) + (v.w >= top2[j][u]);
+        }
+        float best = -INFINITY;
+        if (c1 >= k) best = top1[j][u];
+        if (c2 >= k) best = fmaxf(best, top2[j][u]);
+        best = row_max16(best);
+        if (lane_tok && l16 == 0) bar_s[tok0[j] + u] = best - fmaf(fabsf(best), 0x1p-20f, 0x1p-16f);
       }
-      float best = -INFINITY;
-      if (c1 >= k) best = top1[u];
-      if (c2 >= k) best = fmaxf(best, top2[u]);
-      best = row_max16(best);
-      if (lane_tok && l16 == 0) bar_s[tok0 + u] = best;
-    }
-    __syncthreads();
-    float bar[TPL];
-#pragma unroll
-    for (int u = 0; u < TPL; ++u) bar[u] = bar_s[tok0 + u];
 
     // ---- pass 3: scores >= bar join their token's list
     const int own_tok = tid / LPT, own_str = tid % LPT;
-    sweep(gm.n_init, t_end, [&](int t0, f32x4 (&acc)[4]) {
-#pragma unroll
-      for (int nt = 0; nt < 4; ++nt) {
-        const int t = t0 + nt * 16 + l16;
-#pragma unroll
-        for (int u = 0; u < TPL; ++u) {
-          const float sv = group(acc[nt], u);
-          if (lane_tok && t < lo_t[u] && sv >= bar[u])
-            cand[tok0 + u][atomicAdd(&ccnt[tok0 + u], 1)] = make_float2(sv, __int_as_float(t));
-        }
-      }
-      __syncthreads();
-      // a list that the next chunk could overflow keeps its k best (the staging
-      // buffer is free until the next chunk is staged) and raises its bar
+    // lists that the next chunk could overflow keep their k best (in the staging
+    // area, free between chunks) and raise their bar
+    auto cut_full = [&] {
+      if (!full_s) return;  // the same for every thread: set before the barrier
       const int n_own = ccnt[own_tok];
       const bool cut = n_own > CAP - CH;
       if (cut)
         for (int e = own_str; e < n_own; e += LPT) {
-          const float2 me = cand[own_tok][e];
+          const uint64_t me = cand[own_tok][e];
           int rk = 0;
-          for (int f = 0; f < n_own; ++f) {
-            const float2 o = cand[own_tok][f];
-            rk += beats(o.x, __float_as_int(o.y), me.x, __float_as_int(me.y));
-          }
-          if (rk < k) {
-            tops[own_tok * 2 * KMAX + 2 * rk] = me.x;
-            tops[own_tok * 2 * KMAX + 2 * rk + 1] = me.y;
-          }
+          for (int f = 0; f < n_own; ++f) rk += cand[own_tok][f] > me;
+          if (rk < k) best_k[own_tok * KMAX + rk] = me;
         }
-      __syncthreads();
+      lds_barrier();
       if (cut) {
-        for (int r = own_str; r < k; r += LPT)
-          cand[own_tok][r] = make_float2(tops[own_tok * 2 * KMAX + 2 * r], tops[own_tok * 2 * KMAX + 2 * r + 1]);
+        for (int r = own_str; r < k; r += LPT) cand[own_tok][r] = best_k[own_tok * KMAX + r];
         if (own_str == 0) {
           ccnt[own_tok] = k;
-          bar_s[own_tok] = tops[own_tok * 2 * KMAX + 2 * (k - 1)];
+          bar_s[own_tok] = key_entry(best_k[own_tok * KMAX + k - 1]).x;
         }
       }
-      __syncthreads();
+      if (tid == 0) full_s = 0;
+      lds_barrier();
+    };
+    // a token's list belongs to one quarter-wave: its passing lanes take the next
+    // slots in lane order (an LDS counter per token, with its round trip per
+    // append, took twice the time of the products)
+    sweep(gm.n_init, t_end, std::true_type{}, cut_full, [&](int t0, f32x4 (&acc)[RT][4]) {
 #pragma unroll
-      for (int u = 0; u < TPL; ++u) bar[u] = bar_s[tok0 + u];
+      for (int j = 0; j < RT; ++j)
+#pragma unroll
+        for (int u = 0; u < TPL; ++u) {
+          const int tok = tok0[j] + u;
+          const float bar = bar_s[tok];
+          int cnt = ccnt[tok];
+#pragma unroll
+          for (int nt = 0; nt < 4; ++nt) {
+            const int t = t0 + nt * 16 + l16;
+            const float sv = group(acc[j][nt], lse[j], u);
+            const bool in = lane_tok && t < lo_t[j][u] && sv >= bar;
+            const uint64_t m = __builtin_amdgcn_ballot_w64(in);
+            if (m) {
+              const uint32_t mine = ((q4 & 2 ? (uint32_t)(m >> 32) : (uint32_t)m) >> (16 * (q4 & 1))) & 0xffffu;
+              if (in) cand[tok][cnt + __popc(mine & ((1u << l16) - 1u))] = cand_key(make_float2(sv, __int_as_float(0xffff - t)));
+              cnt += __popc(mine);
+            }
+          }
+          if (lane_tok && l16 == 0) {
+            ccnt[tok] = cnt;
+            if (cnt > CAP - CH) full_s = 1;
+          }
+        }
     });
   }
 
-  // ---- the k best of each token's list, then its row
+  // ---- the k best of each token's list, then its row: LPT threads per token
+  // (one, sorting its picks, took 60 of a long tile's 160 thousand cycles)
   __syncthreads();
-  {
-    const int own_tok = tid / LPT, own_str = tid % LPT;
-    const int n = ccnt[own_tok];
-    for (int e = own_str; e < n; e += LPT) {
-      const float2 me = cand[own_tok][e];
-      int rk = 0;
-      for (int f = 0; f < n; ++f) {
-        const float2 o = cand[own_tok][f];
-        rk += beats(o.x, __float_as_int(o.y), me.x, __float_as_int(me.y));
-      }
-      if (rk < k) picks[own_tok][rk] = __float_as_int(me.y);
+  const int own_tok = tid / LPT, own_str = tid % LPT;
+  const int n = ccnt[own_tok], np = min(k, n);
+  const uint64_t *cl = cand[own_tok];
+  constexpr int E = 8;  // entries a thread ranks at once
+  for (int e0 = own_str; e0 < n; e0 += LPT * E) {
+    uint64_t me[E];
+    int rk[E];
+#pragma unroll
+    for (int x = 0; x < E; ++x) {
+      me[x] = cl[min(e0 + LPT * x, n - 1)];
+      rk[x] = 0;
     }
+    for (int f = 0; f < n; f += 4) {
+      uint64_t o[4];
+#pragma unroll
+      for (int y = 0; y < 4; ++y) o[y] = f + y < n ? cl[f + y] : 0ull;  // below every key
+#pragma unroll
+      for (int y = 0; y < 4; ++y)
+#pragma unroll
+        for (int x = 0; x < E; ++x) rk[x] += o[y] > me[x];
+    }
+#pragma unroll
+    for (int x = 0; x < E; ++x)
+      if (e0 + LPT * x < n && rk[x] < k) picks[own_tok][rk[x]] = key_block(me[x]);
   }
   __syncthreads();
-  if (tid >= NTOK) return;
-  const int i = i0 + tid;
+  const int i = i0 + own_tok;
   if (i >= gm.Lq) return;
+  int32_t *out = sel + ((int64_t)bg * gm.Lq + i) * gm.ksel;
   const int cur = (gm.q_pos0 + i) / gm.m;
-  emit_row(sel + ((int64_t)bg * gm.Lq + i) * gm.ksel, picks[tid], min(k, ccnt[tid]), cur, gm);
+  const int ni = min(gm.n_init, cur + 1), lstart = max(max(0, cur - gm.window / gm.m), ni);
+  for (int p = own_str; p < np; p += LPT) {
+    const int me = picks[own_tok][p];
+    int at = ni;
+#pragma unroll
+    for (int x = 0; x < KMAX; ++x) at += x < np && picks[own_tok][x] < me;
+    out[at] = me;
+  }
+  for (int x = own_str; x < gm.ksel - np; x += LPT) {  // forced blocks and padding around the picks
+    const int l = lstart + x - ni;
+    out[x < ni ? x : x + np] = x < ni ? x : l <= cur ? l : -1;
+  }
 }
 
 // bf16 inputs: scoring on the matrix cores, selection by a bar and a short exact rank.
@@ -784,25 +913,6 @@ __device__ __forceinline__ uint64_t row_ror64(uint64_t v, int r) {
   }
   return ((uint64_t)hi << 32) | lo;
 }
-
-// A candidate list entry is (score, (q4 << 16) | (0xffff - block)): q4 names
-// the entry's row among the four rows that share the list.  For ranking, an
-// entry becomes a 64-bit key: the score's float32 bits mapped to an
-// order-preserving unsigned integer in the high word (-0 counted as +0), the
-// same low word.  For two entries of one row the key order is the selection's
-// order (score descending, then block ascending), so a rank is one 64-bit
-// compare.
-__device__ __forceinline__ uint64_t cand_key(float2 e) {
-  const uint32_t b = __float_as_uint(e.x + 0.f);
-  const uint32_t hi = (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-  return ((uint64_t)hi << 32) | __float_as_uint(e.y);
-}
-__device__ __forceinline__ float2 key_entry(uint64_t key) {
-  const uint32_t hi = (uint32_t)(key >> 32);
-  return make_float2(__uint_as_float((hi & 0x80000000u) ? (hi & 0x7fffffffu) : ~hi), __uint_as_float((uint32_t)key));
-}
-__device__ __forceinline__ int key_row(uint64_t key) { return ((uint32_t)key >> 16) & 3; }
-__device__ __forceinline__ int key_block(uint64_t key) { return 0xffff - ((uint32_t)key & 0xffff); }
 
 // Cuts a 4-row candidate list (n entries in LDS) to the k best entries of each
 // row, keeping their order; ks[q] receives row q's k-th score (-inf for a row
@@ -1366,15 +1476,18 @@ static hipError_t launch_select_softmax_mfma(const Geom &g, const void *Q, const
                        n / 8);
     timing_end(s);
   }
-  constexpr int NTOK = 64 / G;
-  const dim3 grid((g.Lq + NTOK - 1) / NTOK, g.B * g.Hkv);
+  // two row tiles per wave where the lists fit beside two workgroups per CU
+  constexpr int RT = G >= 2 ? 2 : 1;
   timing_begin("phsa_select_softmax", s);
-  if (g.top_k <= 16)
-    hipLaunchKernelGGL((select_softmax_mfma_kernel<D, G, 16>), grid, dim3(256), 0, s,
-                       static_cast<const bf16_t *>(Q), mh, ml, sel, g);
-  else
-    hipLaunchKernelGGL((select_softmax_mfma_kernel<D, G, 32>), grid, dim3(256), 0, s,
-                       static_cast<const bf16_t *>(Q), mh, ml, sel, g);
+  if (g.top_k <= 16) {
+    constexpr int NTOK = 64 * RT / G;
+    hipLaunchKernelGGL((select_softmax_mfma_kernel<D, G, 16, RT>), dim3((g.Lq + NTOK - 1) / NTOK, g.B * g.Hkv), dim3(256),
+                       0, s, static_cast<const bf16_t *>(Q), mh, ml, mnorm, sel, g);
+  } else {
+    constexpr int NTOK = 64 / G;
+    hipLaunchKernelGGL((select_softmax_mfma_kernel<D, G, 32, 1>), dim3((g.Lq + NTOK - 1) / NTOK, g.B * g.Hkv), dim3(256),
+                       0, s, static_cast<const bf16_t *>(Q), mh, ml, mnorm, sel, g);
+  }
   timing_end(s);
   return hipGetLastError();
 }
