@@ -109,7 +109,8 @@ typedef enum {
    * not been modified since.  The inverted selection index that call built
    * (the first part of the workspace) is reused instead of rebuilt; the rest of
    * the workspace is overwritten.  ws_bytes must still cover
-   * phsa_workspace_size(p, PHSA_OP_ATTN_BWD). */
+   * phsa_workspace_size(p, PHSA_OP_ATTN_BWD).  float32: accepted without effect
+   * (the forward builds no index). */
   PHSA_FLAG_REUSE_INDEX = 1,
   /* phsa_select, phsa_forward, phsa_decode, phsa_decode_varlen: rank blocks
    * by Eq. 8's softmax taken per query head and summed over the heads that
@@ -187,7 +188,8 @@ PHSA_API phsa_status phsa_forward(const phsa_params *p, const void *Q, const voi
 /* One decode step (generation with a block KV cache): Lq must be 1, the
  * query sits at position Lk - 1.  K_comp [B, Hkv, T, d] holds the cache's
  * block representatives (from phsa_compress).  Writes sel [B, Hkv, 1, Ksel],
- * O [B, 1, Hq, d] and LSE [B, Hq, 1]. */
+ * O [B, 1, Hq, d] and LSE [B, Hq, 1].  O's bytes may hold intermediate values
+ * until the call's work is complete on `stream`; O may be Q itself. */
 PHSA_API phsa_status phsa_decode(const phsa_params *p, const void *Q, const void *K_cache,
                         const void *V_cache, const float *K_comp, int32_t *sel, void *O,
                         float *LSE, void *ws, size_t ws_bytes, void *stream);
