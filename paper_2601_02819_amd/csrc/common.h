@@ -44,12 +44,31 @@ __device__ __forceinline__ f32x4 mfma16x16x32(const bf16x8 &a, const bf16x8 &b, 
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-// Bit j of a 64-bit mask, j differing between lanes.  Not `mask >> j`: a 64-bit
-// shift (v_lshlrev_b64 / v_lshrrev_b64) whose amount sits in the last register
-// of the wave's allocation takes it from v0 instead on this GPU (cache_append
-// pooled wrong keys, now and then, when its shift came to lie in v71 of 72).
+// No 64-bit shift here takes its amount from a vector register: one
+// (v_lshlrev_b64 / v_lshrrev_b64) whose amount sits in the last register of the
+// wave's allocation takes it from v0 instead on this GPU (cache_append pooled
+// wrong keys, now and then, when its shift came to lie in v71 of 72), and the
+// register is the compiler's choice.  Per-lane bits of wave masks go through the
+// helpers below; a test looks for such shifts in the built library.
+
+// Bit j of a 64-bit mask, j differing between lanes.  The empty asm hides that
+// the halves are one value, which the compiler would shift by (j & 32) again.
 __device__ __forceinline__ bool lane_bit(uint64_t mask, int j) {
-  return ((j & 32 ? (uint32_t)(mask >> 32) : (uint32_t)mask) >> (j & 31)) & 1u;
+  uint32_t hi = (uint32_t)(mask >> 32);
+  asm("" : "+v"(hi));
+  return ((j & 32 ? hi : (uint32_t)mask) >> (j & 31)) & 1u;
+}
+
+// Set bits of a mask below this lane.
+__device__ __forceinline__ int bits_below(uint64_t m) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// The 16 bits of a wave mask that belong to quarter-wave q4 (this lane's).
+__device__ __forceinline__ uint32_t quarter_bits(uint64_t m, int q4) {
+  uint32_t hi = (uint32_t)(m >> 32);
+  asm("" : "+v"(hi));
+  return ((q4 & 2 ? hi : (uint32_t)m) >> (16 * (q4 & 1))) & 0xffffu;
 }
 
 // 16-byte load of data that is read once (bypasses cache retention).

@@ -137,7 +137,7 @@ __device__ __forceinline__ int wave_rank_k(float2 *list, int n, int k, int lane,
     for (int l = 0; l < n; ++l) rank += (l < lane) & (__builtin_amdgcn_readlane(key, l) == key);
     m = __ballot(have && rank < k);
   }
-  const int at = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+  const int at = bits_below(m);
   wave_lds_sync();
   if (__builtin_amdgcn_inverse_ballot_w64(m)) list[at] = me;
   wave_lds_sync();
@@ -172,7 +172,7 @@ __device__ __forceinline__ int wave_top_k(const float *sc, int nc, int k, int la
   for (int j = 0; j < PER; ++j) {
     const bool in = j * 64 + lane < nc && v[j] >= bar;
     const uint64_t m = __ballot(in);
-    const int at = n + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+    const int at = n + bits_below(m);
     if (in && at < 64) list[at] = make_float2(v[j], __int_as_float(j * 64 + lane));
     n += __popcll(m);
   }

@@ -115,7 +115,7 @@ __device__ __forceinline__ RowEntries row_entries(int t, int i, const Geom &gm, 
   const int prev = from_lane_below(tc);
   const bool first = valid && (lane == 0 || prev != tc);
   const uint64_t heads = __ballot(first);
-  e.pos = __popcll(heads & ((1ull << lane) - 1ull));
+  e.pos = bits_below(heads);
   e.n = __popcll(heads);
   unsigned acc = qb;
   int oq = (int)qb, otc = tc;  // the values of lane + dd
@@ -495,7 +495,7 @@ __global__ __launch_bounds__(256) void index_fill_kernel(const int32_t *__restri
   // rows of the tile below row r (word r / 32, bit r % 32) that chose t
   auto rank_of = [&](int t, int r) {
     const int word = r >> 5;
-    return (int)((pre_s[t] >> (8 * word)) & 0xffu) + __popc(bm[word * gm.T + t] & ((1u << (r & 31)) - 1u));
+    return (int)reinterpret_cast<const uint8_t *>(&pre_s[t])[word] + __popc(bm[word * gm.T + t] & ((1u << (r & 31)) - 1u));
   };
   const int ks = sel_width(gm);
   const int nrow = min(kIndexTile, gm.Lq - w * kIndexTile);

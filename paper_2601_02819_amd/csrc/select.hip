@@ -766,7 +766,7 @@ __global__ __launch_bounds__(256, (KMAX > 16 && G == 1 ? 1 : 2)) void select_sof
             const bool in = lane_tok && t < lo_t[j][u] && sv >= bar;
             const uint64_t m = __builtin_amdgcn_ballot_w64(in);
             if (m) {
-              const uint32_t mine = ((q4 & 2 ? (uint32_t)(m >> 32) : (uint32_t)m) >> (16 * (q4 & 1))) & 0xffffu;
+              const uint32_t mine = quarter_bits(m, q4);
               if (in) cand[tok][cnt + __popc(mine & ((1u << l16) - 1u))] = cand_key(make_float2(sv, __int_as_float(0xffff - t)));
               cnt += __popc(mine);
             }
@@ -922,7 +922,6 @@ template <int C4>
 __device__ __noinline__ int compact_list(float2 *lp, int n, int k, float *ks) {
   constexpr int U = (C4 + 63) / 64;
   const int lane = threadIdx.x & 63;
-  const uint64_t below = (1ull << lane) - 1ull;
   uint64_t *kp = reinterpret_cast<uint64_t *>(lp);  // the same bytes, as keys
   if (lane < 4) ks[lane] = -INFINITY;
   uint64_t ent[U];
@@ -953,7 +952,7 @@ __device__ __noinline__ int compact_list(float2 *lp, int n, int k, float *ks) {
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const uint64_t m = __builtin_amdgcn_ballot_w64(keep[u]);
-    if (keep[u]) lp[pos + __popcll(m & below)] = key_entry(ent[u]);
+    if (keep[u]) lp[pos + bits_below(m)] = key_entry(ent[u]);
     pos += __popcll(m);
   }
   wave_lds_sync();
@@ -992,8 +991,7 @@ __global__ __launch_bounds__(NW * 64) void select_mfma_kernel(const bf16_t *__re
   const int bg = wo.bg, b = bg / gm.Hkv, g = bg % gm.Hkv;
   const int i0 = wo.tile * ROWS;
   const int k = gm.top_k;
-  const uint64_t grp_bits = 0xffffull << (16 * q4);
-  const uint64_t below = (1ull << lane) - 1ull;
+  const uint32_t below = (1u << l16) - 1u;  // lower lanes of this quarter-wave
   // tile row of accumulator entry (j, r) held by this lane: 32 w + 16 j + 4 q4 + r
   auto crow = [&](int rr) { return wave * 16 * RT + (rr >> 2) * 16 + q4 * 4 + (rr & 3); };
   const bf16_t *mh_bg = Mh_g + (int64_t)bg * gm.T * D;
@@ -1320,7 +1318,7 @@ __global__ __launch_bounds__(NW * 64) void select_mfma_kernel(const bf16_t *__re
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const uint64_t m = __builtin_amdgcn_ballot_w64(tg == q);
-        if (tg == q) split[off[q] + __popcll(m & below)] = ent;
+        if (tg == q) split[off[q] + bits_below(m)] = ent;
         off[q] += __popcll(m);
       }
     }
@@ -1356,10 +1354,10 @@ __global__ __launch_bounds__(NW * 64) void select_mfma_kernel(const bf16_t *__re
         }
       }
       const bool take0 = l16 < my_n && r0 < k, take1 = l16 + 16 < my_n && r1 < k;
-      const uint64_t m0 = __builtin_amdgcn_ballot_w64(take0) & grp_bits;
-      const uint64_t m1 = __builtin_amdgcn_ballot_w64(take1) & grp_bits;
-      if (take0 && live) out[ni + __popcll(m0 & below)] = key_block(k0);
-      if (take1 && live) out[ni + __popcll(m0) + __popcll(m1 & below)] = key_block(k1);
+      const uint32_t m0 = quarter_bits(__builtin_amdgcn_ballot_w64(take0), q4);
+      const uint32_t m1 = quarter_bits(__builtin_amdgcn_ballot_w64(take1), q4);
+      if (take0 && live) out[ni + __popc(m0 & below)] = key_block(k0);
+      if (take1 && live) out[ni + __popc(m0) + __popc(m1 & below)] = key_block(k1);
     } else {
       // longer lists (many equal scores): rank against every entry through LDS
       for (int j0 = 0; j0 < max_n; j0 += 16) {
@@ -1369,9 +1367,9 @@ __global__ __launch_bounds__(NW * 64) void select_mfma_kernel(const bf16_t *__re
         int rk = 0;
         for (int f = 0; f < max_n; ++f) rk += (f < my_n) & (rp[min(f, max(my_n - 1, 0))] > me);
         const bool take = have && rk < k;
-        const uint64_t m = __builtin_amdgcn_ballot_w64(take) & grp_bits;
-        if (take && live) out[ni + pos + __popcll(m & below)] = key_block(me);
-        pos += __popcll(m);
+        const uint32_t m = quarter_bits(__builtin_amdgcn_ballot_w64(take), q4);
+        if (take && live) out[ni + pos + __popc(m & below)] = key_block(me);
+        pos += __popc(m);
       }
     }
     // forced init blocks, local blocks and padding around the picks
