@@ -252,6 +252,9 @@ __device__ __forceinline__ f32x4 mfma_f32(float a, float b, const f32x4 &c) {
 //                            lane (q, j) contracting features q D/4 .. + D/4 - 1)
 //   dV^T += dO^T P, dK^T += Q^T dS: register r of P (rows 4 q + r) is the B
 //                            operand of step r, dO^T and Q^T come from LDS.
+// A key takes nothing from a row that may not see it: its weight is zero, and in a
+// chunk whose Q or dO holds an infinity or NaN, which a zero weight would not
+// stop in a product, the last two sums run row by row and leave such rows out.
 template <int D, int G, int M>
 __global__ __launch_bounds__(256) void attn_dkv_fp32_kernel(const float *__restrict__ Q, const float *__restrict__ K,
                                                             const float *__restrict__ V,
@@ -268,6 +271,7 @@ __global__ __launch_bounds__(256) void attn_dkv_fp32_kernel(const float *__restr
   __shared__ __attribute__((aligned(16))) float Qs[ROWS * P], Os[ROWS * P];
   __shared__ float lse_s[ROWS], dd_s[ROWS];
   __shared__ int pos_s[ROWS];
+  __shared__ int odd_s[4];               // wave w staged an infinity or NaN
   const int u = blockIdx.x;
   const int4 unit = ix.units[u];
   if (u % ix.units_bg >= ix.ucnt[u / ix.units_bg]) return;
@@ -315,12 +319,17 @@ __global__ __launch_bounds__(256) void attn_dkv_fp32_kernel(const float *__restr
   const float sl2 = gm.scale * kLog2e;
   for (int r0 = 0; r0 < n_rows; r0 += ROWS) {
     __syncthreads();
+    f32x4 z = f32x4{0.f, 0.f, 0.f, 0.f};  // 0 x (finite) stays 0
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
       const int x = tid + 256 * k, r = x / VPR, c = (x % VPR) * 4;
       *reinterpret_cast<f32x4 *>(&Qs[r * P + c]) = pq[k];
       *reinterpret_cast<f32x4 *>(&Os[r * P + c]) = po[k];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) z[e] = fmaf(pq[k][e], 0.f, fmaf(po[k][e], 0.f, z[e]));
     }
+    const uint64_t odd_m = __ballot(!(z[0] + z[1] + (z[2] + z[3]) == 0.f));
+    if (lane == 0) odd_s[wave] = odd_m != 0;
     if (tid < ROWS) {
       lse_s[tid] = pl;
       dd_s[tid] = pd;
@@ -345,8 +354,30 @@ __global__ __launch_bounds__(256) void attn_dkv_fp32_kernel(const float *__restr
     for (int r = 0; r < 4; ++r) {
       const int x = rt * 16 + q4 * 4 + r;
       const float w = __builtin_amdgcn_exp2f(fmaf(s[r], sl2, -lse_s[x]));
-      p[r] = key <= pos_s[x] ? w : 0.f;
-      ds[r] = p[r] * (dp[r] - dd_s[x]);
+      const bool sees = key <= pos_s[x];
+      p[r] = sees ? w : 0.f;
+      ds[r] = sees ? w * (dp[r] - dd_s[x]) : 0.f;
+    }
+    if (__builtin_amdgcn_readfirstlane(odd_s[0] | odd_s[1] | odd_s[2] | odd_s[3])) {
+#pragma unroll 1
+      for (int xq = 0; xq < 4; ++xq)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int x = rt * 16 + xq * 4 + r;
+          const float px = __shfl(p[r], xq * 16 + l16, 64), dx = __shfl(ds[r], xq * 16 + l16, 64);
+          if (key > pos_s[x]) continue;
+#pragma unroll
+          for (int n = 0; n < NT; ++n) {
+            const f32x4 ov = *reinterpret_cast<const f32x4 *>(&Os[x * P + n * 16 + q4 * 4]);
+            const f32x4 qv = *reinterpret_cast<const f32x4 *>(&Qs[x * P + n * 16 + q4 * 4]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              dv[n][e] = fmaf(ov[e], px, dv[n][e]);
+              dk[n][e] = fmaf(qv[e], dx, dk[n][e]);
+            }
+          }
+        }
+      continue;
     }
     // features x keys: A = dO^T (lane: feature l16 of the tile, row 4 q + r), B = P
 #pragma unroll
