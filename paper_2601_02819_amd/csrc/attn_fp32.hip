@@ -136,12 +136,13 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_fp32_kernel(const float *__r
       // each key group of lanes keeps a maximum of its own (mn is the same in
       // the CPR lanes of a key); they meet at the end
       const float f = mn == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(mrun[h] - mn);  // 2^-inf = 0 at the first key
+      const float mz = mn == -INFINITY ? 0.f : mn;  // every score -inf so far (an infinite key): weight 0, not NaN
       mrun[h] = mn;
       lrun[h] *= f;
       o[h] *= f;
 #pragma unroll
       for (int n = 0; n < NI; ++n) {
-        const float p = ok[n] ? __builtin_amdgcn_exp2f(sc[n] - mn) : 0.f;
+        const float p = ok[n] ? __builtin_amdgcn_exp2f(sc[n] - mz) : 0.f;
         lrun[h] += p;
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[h][e] = ok[n] ? fmaf(p, vr[n][e], o[h][e]) : o[h][e];

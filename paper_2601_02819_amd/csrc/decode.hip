@@ -536,15 +536,16 @@ __global__ __launch_bounds__(NW * 64, (kDecodeSmall<T, G, MODE> ? 4 : 2)) void d
         }
         // every key group of lanes keeps a maximum of its own (equal in the CPR
         // lanes of a key); they meet at the end.  mn stays -inf only while every
-        // key so far was masked: nothing has been accumulated yet.
+        // key so far was masked or scored -inf (an infinite key): weights 0.
         const float f = mn == -INFINITY ? 1.f : __builtin_amdgcn_exp2f(mrun[h] - mn);
+        const float mz = mn == -INFINITY ? 0.f : mn;
         mrun[h] = mn;
         lrun[h] *= f;
         o[h] *= f;
         // keys past the query (the unwritten tail of its own block) add nothing
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
-          const float p = (okm >> i) & 1 ? __builtin_amdgcn_exp2f(s[i] - mn) : 0.f;
+          const float p = (okm >> i) & 1 ? __builtin_amdgcn_exp2f(s[i] - mz) : 0.f;
           lrun[h] += p;
 #pragma unroll
           for (int e = 0; e < VEC; ++e) o[h][e] = fmaf(p, vr[i][e], o[h][e]);
