@@ -407,9 +407,10 @@ __global__ __launch_bounds__(NW * 64, (kDecodeSmall<T, G, MODE> ? 4 : 2)) void d
     // Matrix cores: 32 keys at a time, S^T = K Q^T (keys x heads; the G heads
     // fill G of 16 columns) with K straight from memory as the A operand, and
     // O^T = V^T P^T with V copied into the wave's LDS area and read transposed.
-    // P is split into bf16 hi + lo, two products, so that it keeps 16 bits of
-    // mantissa.  (On the vector ALUs, lane = feature, the products of one
-    // workgroup took 14000 of 25000 cycles at 1 x 8k.)
+    // P is split into three bf16 parts, three products: 8 + 8 + 8 bits hold its
+    // float32 mantissa, so O is the sum of the weights that LSE counts.  (On the vector
+    // ALUs, lane = feature, the products of one workgroup took 14000 of 25000
+    // cycles at 1 x 8k.)
     constexpr int KB = D / 32, NT = D / 16;
     bf16_t *Vs = reinterpret_cast<bf16_t *>(wo);  // [32][D], swizzled
     const int l16 = lane & 15, q4 = lane >> 4;
@@ -461,26 +462,28 @@ __global__ __launch_bounds__(NW * 64, (kDecodeSmall<T, G, MODE> ? 4 : 2)) void d
       const float mz = mn == -INFINITY ? 0.f : mn;
       mrun = mn;
       lrun *= f;
-      f32x4 lo[2];
+      f32x4 mid[2], lo[2];
 #pragma unroll
       for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const float p = __builtin_amdgcn_exp2f(st[kt][r] - mz);
           lrun += p;
-          const float h = bf16_to_f32(f32_to_bf16(p));
+          const float h = bf16_to_f32(f32_to_bf16(p)), d1 = p - h, h1 = bf16_to_f32(f32_to_bf16(d1));
           st[kt][r] = h;
-          lo[kt][r] = p - h;
+          mid[kt][r] = h1;
+          lo[kt][r] = d1 - h1;
         }
-      const bf16x8 ph = pack_bf16x8(st[0], st[1]), pl = pack_bf16x8(lo[0], lo[1]);
+      const bf16x8 ph = pack_bf16x8(st[0], st[1]), pm = pack_bf16x8(mid[0], mid[1]), pl = pack_bf16x8(lo[0], lo[1]);
       dma_wait();
       wave_lds_sync();
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) {
         const bf16x8 vt = lds_col8_sw<D>(Vs, q4 * 4, 16 + q4 * 4, nt * 16, l16);
         o[nt] *= f;
-        o[nt] = mfma16x16x32(vt, ph, o[nt]);
         o[nt] = mfma16x16x32(vt, pl, o[nt]);
+        o[nt] = mfma16x16x32(vt, pm, o[nt]);
+        o[nt] = mfma16x16x32(vt, ph, o[nt]);
       }
     }
     lrun += __shfl_xor(lrun, 16, 64);
