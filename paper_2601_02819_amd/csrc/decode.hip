@@ -489,13 +489,50 @@ __global__ __launch_bounds__(NW * 64, (kDecodeSmall<T, G, MODE> ? 4 : 2)) void d
     lrun += __shfl_xor(lrun, 16, 64);
     lrun += __shfl_xor(lrun, 32, 64);
     wave_lds_sync();
-    if (l16 < G) {  // lane (q, j) holds features 16 nt + 4 q .. + 3 of head j
+    bool odd = false;
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) odd |= !(o[nt][r] == o[nt][r]);
+    if (__builtin_expect(__ballot(odd && l16 < G) != 0, 0)) {
+      // An infinite value met a zero part or a masked key in the products
+      // (0 x inf): this wave's keys again, one after another.
+      constexpr int E = D / 64;  // features lane E .. + E - 1 of every head
+      float acc[G][E];
+#pragma unroll
+      for (int h = 0; h < G; ++h)
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[h][e] = 0.f;
+#pragma unroll 1
+      for (int x0 = wave * 32; x0 < nkeys; x0 += NW * 32)
+#pragma unroll 1
+        for (int x = x0; x < min(x0 + 32, nkeys); ++x) {
+          const int key = (__builtin_amdgcn_readfirstlane(slot_s[x >> msh]) << msh) + (x & (gm.m - 1));
+          if (key > pos) break;
+#pragma unroll
+          for (int h = 0; h < G; ++h) {
+            float a = 0.f;
+#pragma unroll
+            for (int e = 0; e < E; ++e) a = fmaf(to_f32<T>(Qg[h * D + lane * E + e]), to_f32<T>(Kb[key * kstep + lane * E + e]), a);
+#pragma unroll
+            for (int y = 1; y < 64; y <<= 1) a += __shfl_xor(a, y, 64);
+            const float mh = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(mrun), h));
+            const float p = __builtin_amdgcn_exp2f(a * sl2 - (mh == -INFINITY ? 0.f : mh));
+#pragma unroll
+            for (int e = 0; e < E; ++e) acc[h][e] = fmaf(p, to_f32<T>(Vb[key * kstep + lane * E + e]), acc[h][e]);
+          }
+        }
+#pragma unroll
+      for (int h = 0; h < G; ++h)
+#pragma unroll
+        for (int e = 0; e < E; ++e) wo[h * D + lane * E + e] = acc[h][e];
+    } else if (l16 < G) {  // lane (q, j) holds features 16 nt + 4 q .. + 3 of head j
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt) *reinterpret_cast<f32x4 *>(wo + l16 * D + nt * 16 + q4 * 4) = o[nt];
-      if (q4 == 0) {
-        wm[wave][l16] = mrun;
-        wl[wave][l16] = lrun;
-      }
+    }
+    if (l16 < G && q4 == 0) {
+      wm[wave][l16] = mrun;
+      wl[wave][l16] = lrun;
     }
   } else {
     // float32: load unit u covers KPI keys (blocks are multiples of 16 keys, so a
@@ -545,13 +582,15 @@ __global__ __launch_bounds__(NW * 64, (kDecodeSmall<T, G, MODE> ? 4 : 2)) void d
         mrun[h] = mn;
         lrun[h] *= f;
         o[h] *= f;
-        // keys past the query (the unwritten tail of its own block) add nothing
+        // keys past the query (the unwritten tail of its own block) add nothing;
+        // their loads repeat the query's own value, which may be infinite
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
-          const float p = (okm >> i) & 1 ? __builtin_amdgcn_exp2f(s[i] - mz) : 0.f;
+          const bool ok = (okm >> i) & 1;
+          const float p = ok ? __builtin_amdgcn_exp2f(s[i] - mz) : 0.f;
           lrun[h] += p;
 #pragma unroll
-          for (int e = 0; e < VEC; ++e) o[h][e] = fmaf(p, vr[i][e], o[h][e]);
+          for (int e = 0; e < VEC; ++e) o[h][e] = ok ? fmaf(p, vr[i][e], o[h][e]) : o[h][e];
         }
       }
     }

@@ -57,3 +57,29 @@ def test_decode_keys_at_minus_infinity(dtype, G, d, m, n):
                                  q_pos0=n - 1)
     same_where_finite(to_np(o), o_r, O_TOL[dtype], "O")
     same_where_finite(to_np(lse), lse_r, O_TOL[dtype], "LSE")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("mode", ["plain", "softmax_sum", "sliced"])
+@pytest.mark.parametrize("G,d,m,n", [(1, 64, 16, 5), (2, 128, 16, 300), (4, 64, 64, 200), (8, 128, 32, 1000)])
+def test_decode_infinite_values(dtype, mode, G, d, m, n):
+    """Values of +-inf at the query's own position, inside a selected block and both
+    signs in one feature (NaN there): O as the oracle has it, finite elsewhere."""
+    L, Hkv, B = (512 if mode == "sliced" else 64) * m, 2, 2
+    log(f"[inf value] decode {dtype} {mode} G={G} d={d} m={m} length {n}")
+    g = torch.Generator().manual_seed(n + G)
+    q = (torch.randn(B, 1, G * Hkv, d, generator=g) * 0.3).to(DT[dtype])
+    k, v = (torch.randn(B, L, Hkv, d, generator=g) for _ in "kv")
+    v[:, n - 1, :, 3] = float("inf")
+    v[:, 1, :, 7] = float("-inf")
+    v[:, n - 1, 0, 9], v[:, 2, 0, 9] = float("inf"), float("-inf")
+    k, v = k.to(DT[dtype]), v.to(DT[dtype])
+    cfg = phsa.Config(block_size=m, top_k=3, n_init_blocks=1, window=0, softmax_sum=mode == "softmax_sum")
+    kc = phsa.compress(k.cuda(), torch.zeros(B, L, dtype=torch.uint8).cuda(), cfg)
+    sel, o, lse = phsa.decode_varlen(q.cuda(), k.cuda(), v.cuda(), kc, torch.full((B,), n, dtype=torch.int32).cuda(), cfg)
+    pad = -(-n // m) * m
+    o_r, lse_r = oracle.attn_fwd(to_np(q), to_np(k)[:, :pad], to_np(v)[:, :pad], sel.cpu().numpy(), m, d ** -0.5,
+                                 q_pos0=n - 1)
+    assert np.isinf(o_r).sum() == (2 * G * Hkv) * B and np.isnan(o_r).sum() == G * B
+    np.testing.assert_allclose(to_np(o), o_r, atol=O_TOL[dtype], rtol=0)
+    np.testing.assert_allclose(to_np(lse), lse_r, atol=O_TOL[dtype], rtol=0)
