@@ -261,6 +261,9 @@ __device__ __forceinline__ void tile_dma(const bf16_t *src, RowOff row_off, bf16
 // other counters are left alone).
 __device__ __forceinline__ void dma_wait() { __builtin_amdgcn_s_waitcnt(0x0f70); }
 
+// Waits for this wave's LDS reads and writes (lgkmcnt(0)).
+__device__ __forceinline__ void lds_wait() { __builtin_amdgcn_s_waitcnt(0xc07f); }
+
 // Packs two 4-element float groups into a bf16 MFMA operand (elements 0..3,
 // then 4..7), rounding to nearest even with the packed conversion instruction.
 typedef float f32x8 __attribute__((ext_vector_type(8)));

@@ -440,7 +440,10 @@ __global__ __launch_bounds__(NW * 64, (kDecodeSmall<T, G, MODE> ? 4 : 2)) void d
         for (int kb = 0; kb < KB; ++kb)
           kf[kt][kb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(
                                                       Kb + min(key0[kt] + l16, pos) * kstep + kb * 32 + q4 * 8));
-      wave_lds_sync();  // the previous tile's transposed reads are done
+      // the previous tile's transposed reads have returned: the copies reach LDS
+      // by another path, which the order of LDS instructions does not cover
+      wave_lds_sync();
+      lds_wait();
       copy_values<D>(Vb, kstep, key0, pos, Vs, lane);
       f32x4 st[2];
       float mn = mrun;
