@@ -270,7 +270,7 @@ __global__ __launch_bounds__(256) void attn_dkv_fp32_kernel(const float *__restr
   constexpr int VPR = D / 4, NV = ROWS * VPR / 256;
   static_assert(NV * 256 == ROWS * VPR, "staging");
   __shared__ __attribute__((aligned(16))) float Qs[ROWS * P], Os[ROWS * P];
-  __shared__ float lse_s[ROWS], dd_s[ROWS];
+  __shared__ float lse_s[ROWS], dd_s[ROWS], times_s[ROWS];  // times: how often the row lists the block
   __shared__ int pos_s[ROWS];
   __shared__ int odd_s[4];               // wave w staged an infinity or NaN
   const int u = blockIdx.x;
@@ -299,7 +299,7 @@ __global__ __launch_bounds__(256) void attn_dkv_fp32_kernel(const float *__restr
   for (int n = 0; n < NT; ++n) dk[n] = dv[n] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   f32x4 pq[NV], po[NV];
-  float pl = 0.f, pd = 0.f;
+  float pl = 0.f, pd = 0.f, pt = 0.f;
   int pp = -1;
   auto fetch = [&](int r0) {  // rows past the unit's end take its last row; they see no key
 #pragma unroll
@@ -310,7 +310,8 @@ __global__ __launch_bounds__(256) void attn_dkv_fp32_kernel(const float *__restr
       po[k] = *reinterpret_cast<const f32x4 *>(dO + src);
     }
     if (tid < ROWS) {
-      const int r = min(r0 + tid, n_rows - 1), i = list[r / G] >> 10, h = g * G + r % G;
+      const int r = min(r0 + tid, n_rows - 1), e = list[r / G], i = e >> 10, h = g * G + r % G;
+      pt = (float)(1 + (e & 63));
       pl = LSE[((int64_t)b * gm.Hq + h) * gm.Lq + i] * kLog2e;
       pd = Dvec[((int64_t)b * gm.Lq + i) * gm.Hq + h];
       pp = r0 + tid < n_rows ? gm.q_pos0 + i : -1;
@@ -334,6 +335,7 @@ __global__ __launch_bounds__(256) void attn_dkv_fp32_kernel(const float *__restr
     if (tid < ROWS) {
       lse_s[tid] = pl;
       dd_s[tid] = pd;
+      times_s[tid] = pt;
       pos_s[tid] = pp;
     }
     __syncthreads();
@@ -354,7 +356,7 @@ __global__ __launch_bounds__(256) void attn_dkv_fp32_kernel(const float *__restr
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int x = rt * 16 + q4 * 4 + r;
-      const float w = __builtin_amdgcn_exp2f(fmaf(s[r], sl2, -lse_s[x]));
+      const float w = times_s[x] * __builtin_amdgcn_exp2f(fmaf(s[r], sl2, -lse_s[x]));
       const bool sees = key <= pos_s[x];
       p[r] = sees ? w : 0.f;
       ds[r] = sees ? w * (dp[r] - dd_s[x]) : 0.f;

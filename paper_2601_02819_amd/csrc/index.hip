@@ -365,31 +365,43 @@ __global__ __launch_bounds__(kScanThreads) void index_scan_kernel(Geom gm, Index
 // ---- selections whose blocks are the index's own (64-token blocks without a
 // band, float32): kScanThreads threads per 256-row tile take the tile's (row,
 // slot) pairs, each pair on its own.  A row's entries are the valid prefix of
-// its sel row; bad_s[r] is the first slot past it.  (One thread per row walking
+// its sel row; bad_s[r] is the first slot past it.  float32 rows (every_slot) keep
+// each valid slot, as the row-major float32 kernels do; a block listed more than
+// once is one entry that counts its copies.  (One thread per row walking
 // its slots took 12 + 20 us for count and fill at 8k tokens and 49 + 85 at 4 x 32k,
 // against 8.5 + 13.7 and 31 + 76; events.)
 
 // The row of pair x (x / ks, by the reciprocal inv = ceil(2^32 / ks); x < 2^14).
 __device__ __forceinline__ int pair_row(int x, int ks, uint32_t inv) { return ks == 1 ? x : (int)__umulhi((uint32_t)x, inv); }
 
+__device__ __forceinline__ bool every_slot(const Geom &gm) { return gm.dtype != 0; }  // float32
+
 // Stages the tile's sel rows, finds bad_s and sets the tile's bitmap bm [8][T].
-__device__ __forceinline__ void pair_bitmap(uint32_t *bm, int32_t *rows_s, int *bad_s, const int32_t *__restrict__ sel,
-                                            const Geom &gm, int ks, uint32_t inv, int bg, int w) {
+// every_slot: an invalid slot is staged as -1 and bad_s stays ks; *twice_s is set
+// when a row lists a block more than once.
+__device__ __forceinline__ void pair_bitmap(uint32_t *bm, int32_t *rows_s, int *bad_s, int *twice_s,
+                                            const int32_t *__restrict__ sel, const Geom &gm, int ks, uint32_t inv,
+                                            int bg, int w) {
   const int tid = threadIdx.x, msh = __builtin_ctz((unsigned)gm.m);
   const int nrow = min(kIndexTile, gm.Lq - w * kIndexTile), n = nrow * ks;
   const int32_t *src = sel + ((int64_t)bg * gm.Lq + (int64_t)w * kIndexTile) * ks;
   for (int x = tid; x < gm.T * 8; x += kScanThreads) bm[x] = 0u;
   if (tid < kIndexTile) bad_s[tid] = ks;
+  if (tid == 0) *twice_s = 0;
   __syncthreads();
   for (int x = tid; x < n; x += kScanThreads) {
     const int r = pair_row(x, ks, inv), t = src[x];
-    rows_s[x] = t;
-    if (!slot_valid(t, (gm.q_pos0 + w * kIndexTile + r) >> msh, gm.T)) atomicMin(&bad_s[r], x - r * ks);
+    const bool ok = slot_valid(t, (gm.q_pos0 + w * kIndexTile + r) >> msh, gm.T);
+    rows_s[x] = ok ? t : -1;
+    if (!ok && !every_slot(gm)) atomicMin(&bad_s[r], x - r * ks);
   }
   __syncthreads();
   for (int x = tid; x < n; x += kScanThreads) {
-    const int r = pair_row(x, ks, inv);
-    if (x - r * ks < bad_s[r]) atomicOr(&bm[(r >> 5) * gm.T + rows_s[x]], 1u << (r & 31));
+    const int r = pair_row(x, ks, inv), t = rows_s[x];
+    if (t < 0 || x - r * ks >= bad_s[r]) continue;
+    uint32_t *word = &bm[(r >> 5) * gm.T + t];
+    if (!every_slot(gm)) atomicOr(word, 1u << (r & 31));
+    else if (atomicOr(word, 1u << (r & 31)) >> (r & 31) & 1u) *twice_s = 1;
   }
   __syncthreads();
 }
@@ -397,9 +409,9 @@ __device__ __forceinline__ void pair_bitmap(uint32_t *bm, int32_t *rows_s, int *
 __global__ __launch_bounds__(kScanThreads) void index_count_pairs_kernel(const int32_t *__restrict__ sel, Geom gm,
                                                                          IndexWs ix, uint32_t inv) {
   extern __shared__ uint32_t bm[];
-  __shared__ int bad_s[kIndexTile];
+  __shared__ int bad_s[kIndexTile], twice_s;
   const int w = blockIdx.x, bg = blockIdx.y;
-  pair_bitmap(bm, reinterpret_cast<int32_t *>(bm + 8 * gm.T), bad_s, sel, gm, gm.ksel, inv, bg, w);
+  pair_bitmap(bm, reinterpret_cast<int32_t *>(bm + 8 * gm.T), bad_s, &twice_s, sel, gm, gm.ksel, inv, bg, w);
   int32_t *dst = ix.cntw + ((int64_t)bg * ix.W + w) * gm.T;
   for (int t = threadIdx.x; t < gm.T; t += kScanThreads) {
     int c = 0;
@@ -415,7 +427,7 @@ template <bool SCAN>
 __global__ __launch_bounds__(kScanThreads) void index_fill_pairs_kernel(const int32_t *__restrict__ sel, Geom gm,
                                                                         IndexWs ix, uint32_t inv, int tp) {
   extern __shared__ uint32_t bm[];
-  __shared__ int bad_s[kIndexTile];
+  __shared__ int bad_s[kIndexTile], twice_s;
   uint64_t *pre_s = reinterpret_cast<uint64_t *>(bm + 8 * gm.T);
   int32_t *base_s = reinterpret_cast<int32_t *>(pre_s + gm.T);
   int32_t *rows_s = base_s + gm.T;
@@ -430,7 +442,7 @@ __global__ __launch_bounds__(kScanThreads) void index_fill_pairs_kernel(const in
     const int32_t *list_off = ix.off + (int64_t)bg * gm.T;
     for (int t = tid; t < gm.T; t += kScanThreads) base_s[t] = list_off[t] + tile_off[t];
   }
-  pair_bitmap(bm, rows_s, bad_s, sel, gm, ks, inv, bg, w);  // its barriers also publish base_s
+  pair_bitmap(bm, rows_s, bad_s, &twice_s, sel, gm, ks, inv, bg, w);  // its barriers also publish base_s
   for (int t = tid; t < gm.T; t += kScanThreads) {
     uint64_t pre = 0;
     int run = 0;  // at most 7 x 32 = 224 rows below the last word
@@ -445,14 +457,20 @@ __global__ __launch_bounds__(kScanThreads) void index_fill_pairs_kernel(const in
   const int n = min(kIndexTile, gm.Lq - w * kIndexTile) * ks;
   int32_t *pm = ix.pmap + ((int64_t)bg * gm.Lq + (int64_t)w * kIndexTile) * ks;
   for (int x = tid; x < n; x += kScanThreads) {
-    const int r = pair_row(x, ks, inv), s = x - r * ks;
+    const int r = pair_row(x, ks, inv), s = x - r * ks, t = rows_s[x];
     int p = -1;
-    if (s < bad_s[r]) {
-      const int t = rows_s[x], word = r >> 5;
+    if (t >= 0 && s < bad_s[r]) {
+      const int word = r >> 5;
       // lower rows of the tile that chose t: those of the lower words (a byte of pre_s) and of its own
       const uint32_t lower = reinterpret_cast<const uint8_t *>(&pre_s[t])[word];
       p = base_s[t] + (int)lower + __popc(bm[word * gm.T + t] & ((1u << (r & 31)) - 1u));
-      ix.tok[p] = ((w * kIndexTile + r) << 10) | (15 << 6) | s;
+      int low = s;
+      if (every_slot(gm)) {  // the slot is not used: further copies of the block in the row
+        low = 0;
+        if (twice_s)
+          for (int y = r * ks; y < (r + 1) * ks; ++y) low += y != x && rows_s[y] == t;
+      }
+      ix.tok[p] = ((w * kIndexTile + r) << 10) | (15 << 6) | low;
     }
     pm[x] = p;
   }

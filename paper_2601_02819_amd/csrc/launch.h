@@ -44,6 +44,7 @@ struct IndexWs {
   int32_t *fin;       // [R, T]         the (b, g, t) whose dK/dV the finalize writes (not one work unit)
   int32_t *fcnt;      // [R]            forward units of (b, g)
   int32_t *tok;       // [nnz_max]      (query row << 10) | (quarter mask << 6) | slot, ascending row per list
+                      //                 (float32: further copies of the block in the row, for the slot)
   int32_t *pmap;      // [B*Hkv*Lq*Ksel] list position of each valid (row, slot); partials are
                       //                 stored in list order and the merges gather through this map
   int4 *units;        // [R, units_bg]  (b*Hkv*T + g*T + t, entries, list position of the first, 1: the whole list)
