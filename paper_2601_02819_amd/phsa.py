@@ -362,14 +362,15 @@ class SparseAttention(torch.autograd.Function):
     """Autograd wrapper: forward = phsa_attn_fwd, backward = phsa_attn_bwd (selection fixed).
 
     The forward's workspace, sized for both passes, is kept for the backward,
-    which then reuses the inverted selection index instead of rebuilding it."""
+    which then reuses the inverted selection index instead of rebuilding it.
+    A float32 forward uses none: nothing is held until the backward."""
 
     @staticmethod
     def forward(ctx, q, k, v, sel, cfg: Config):
         B, Lq, Hq, d = q.shape
         p = make_params(cfg, B, Lq, k.shape[1], Hq, k.shape[2], d, q.dtype)
-        need = max(workspace_size(p, OP_ATTN_FWD), workspace_size(p, OP_ATTN_BWD))
-        ws = torch.empty(need, dtype=torch.uint8, device=q.device) if need else None
+        need = workspace_size(p, OP_ATTN_FWD)
+        ws = torch.empty(max(need, workspace_size(p, OP_ATTN_BWD)), dtype=torch.uint8, device=q.device) if need else None
         o, lse = attn_fwd(q, k, v, sel, cfg, ws)
         ctx.save_for_backward(q, k, v, o, lse, sel)
         ctx.cfg, ctx.ws = cfg, ws
