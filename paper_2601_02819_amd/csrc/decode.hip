@@ -714,10 +714,12 @@ static hipError_t launch_decode_t(const Geom &g, const DecodeArgs &a, hipStream_
 // written to K_comp[b, :, t].  One workgroup per sequence; a sequence whose
 // cache is full is left unchanged.  Rows move in 16-byte chunks; for the
 // pooling, the Hkv*d elements are split into 16-byte chunks and the block's m
-// keys into NTHR / #chunks slices, U rows in flight per thread, whose partial
-// sums meet in LDS.  A chain of memory round trips bounds it (length, row,
-// block), so the block's punctuation flags are one load and a ballot per wave
-// (one thread counting them a byte at a time took the call from 7 to 30 us).
+// keys into NTHR / #chunks slices (at most m), U rows in flight per thread, whose
+// partial sums meet in LDS, a thread per element.  A chain of memory round trips
+// bounds it (length, row, block), so the block's punctuation flags are one load
+// and a ballot per wave (one thread counting them a byte at a time took the call
+// from 7 to 30 us).  When one thread per chunk added the slices' sums, those of
+// a narrow cache (2 heads of 64: 16 threads, 64 slices) took the kernel to 28 us.
 template <typename T, int D>
 __global__ __launch_bounds__(1024) void cache_append_kernel(const T *__restrict__ Kn, const T *__restrict__ Vn,
                                                             const uint8_t *__restrict__ pn, T *__restrict__ Kcache,
@@ -747,7 +749,7 @@ __global__ __launch_bounds__(1024) void cache_append_kernel(const T *__restrict_
     const int np = __popcll(pmask);
     for (int x0 = 0; x0 < NCH; x0 += NTHR) {
       const int nch = min(NTHR, NCH - x0);      // chunks handled in this pass
-      const int slices = NTHR / nch;            // key slices
+      const int slices = min(NTHR / nch, gm.m); // key slices
       const int ch = tid % nch, sl = tid / nch;
       float sum[VEC], psum[VEC];
 #pragma unroll
@@ -782,22 +784,18 @@ __global__ __launch_bounds__(1024) void cache_append_kernel(const T *__restrict_
         red[1][tid][e] = psum[e];
       }
       __syncthreads();
-      if (tid < nch) {
-        float rep[VEC];
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-          float s0 = 0.f, s1 = 0.f;
-          for (int q = 0; q < slices; ++q) {
-            s0 += red[0][q * nch + tid][e];
-            s1 += red[1][q * nch + tid][e];
-          }
-          const float m0 = s0 / (float)gm.m;
-          rep[e] = np > 0 ? gm.lambda * m0 + (1.f - gm.lambda) * (s1 / (float)np) : m0;
+      // one thread per element: slice q's sums start at q * nch * VEC
+      const float *r0 = &red[0][0][0], *r1 = &red[1][0][0];
+      for (int x = tid; x < nch * VEC; x += NTHR) {
+        float s0 = 0.f, s1 = 0.f;
+        for (int q = 0; q < slices; ++q) {
+          s0 += r0[q * nch * VEC + x];
+          s1 += r1[q * nch * VEC + x];
         }
-        const int x = (x0 + tid) * VEC, g = x / D, c = x - g * D;
-        float *dst = Kc + (((int64_t)b * gm.Hkv + g) * gm.T + t) * D + c;
-#pragma unroll
-        for (int e = 0; e < VEC; e += 4) *reinterpret_cast<float4 *>(dst + e) = make_float4(rep[e], rep[e + 1], rep[e + 2], rep[e + 3]);
+        const float m0 = s0 / (float)gm.m;
+        const int at = x0 * VEC + x, g = at / D, c = at - g * D;
+        Kc[(((int64_t)b * gm.Hkv + g) * gm.T + t) * D + c] =
+            np > 0 ? gm.lambda * m0 + (1.f - gm.lambda) * (s1 / (float)np) : m0;
       }
       __syncthreads();
     }
