@@ -44,9 +44,11 @@ size_t index_layout(const Geom &g, char *base, IndexWs *ix) {
   w.nnz_max = R * g.Lq * nsp;
   w.band_base = w.nnz_max;
   w.unit_tokens = unit_size(w.nnz_max, kFillBwd, 128 / g.G, 64 * (64 / g.G));
-  w.units_bg = g.T + (int)(((int64_t)g.Lq * nsp + w.unit_tokens - 1) / w.unit_tokens);
+  // at most: one short unit per block and the full ones (a multiple of 8 for unit_at)
+  auto reserve = [&](int size) { return (g.T + (int)(((int64_t)g.Lq * nsp + size - 1) / size) + 7) / 8 * 8; };
+  w.units_bg = reserve(w.unit_tokens);
   w.fpart = unit_size(w.nnz_max, kFillFwd, 64 / g.G, 512);
-  w.funits_bg = g.T + (int)(((int64_t)g.Lq * nsp + w.fpart - 1) / w.fpart);
+  w.funits_bg = reserve(w.fpart);
   size_t off = 0;
   auto take = [&](size_t bytes) {
     char *p = base ? base + off : nullptr;

@@ -119,10 +119,11 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_sparse_kernel(
   __shared__ __attribute__((aligned(16))) float dd_s[64];
   __shared__ __attribute__((aligned(16))) int pos_s[64];
 
-  const int u = xcd_item(blockIdx.x, gridDim.x);  // the units of one list on one XCD
+  const UnitAt at = unit_at(blockIdx.x, gm.B * gm.Hkv, ix.units_bg);
+  const int u = at.bg * ix.units_bg + at.idx;
   // the unit's record is read beside the count that tells whether it exists
   const int4 unit = ix.units[u];
-  if (u % ix.units_bg >= ix.ucnt[u / ix.units_bg]) return;
+  if (at.idx >= ix.ucnt[at.bg]) return;
   const int bgt = unit.x, n_ent = unit.y;
   const bool whole_block = unit.w;
   const int bg = bgt / gm.T, t = bgt - bg * gm.T;

@@ -30,8 +30,8 @@
 // for a few chunks.  Short units (unit_size in api.hip) keep that chain the
 // longest thing that runs: with units of 2048 entries the list that every row
 // is on (block 0) took 75 us at 1k tokens and 258 us at 8k, against 16 and 113
-// us now.  Units of one block go to one XCD (xcd_item), whose L2 then loads the
-// K/V tile once: 113 against 148 us at 8k, 2.21 against 2.27 ms at 4 x 32k.
+// us now.  The units of a (b, g) go to as few XCDs as a fair share allows
+// (unit_at): 113 against 148 us at 8k, 2.21 against 2.27 ms at 4 x 32k.
 // Splitting the lists by query rows so that a segment's rows stay in an L2 was
 // slower (2.7 ms with 4096-row segments): a tile then meets too few rows.
 //
@@ -67,8 +67,8 @@ __global__ __launch_bounds__(256, 3) void attn_fwd_sparse_kernel(const bf16_t *_
   __shared__ __attribute__((aligned(16))) bf16_t Os[4][16 * SP];  // per-wave partial rows
 
   // this workgroup's unit
-  const int item = xcd_item(blockIdx.x, gridDim.x);
-  const int bg = item / ix.funits_bg, idx = item - bg * ix.funits_bg;
+  const UnitAt at = unit_at(blockIdx.x, gm.B * gm.Hkv, ix.funits_bg);
+  const int bg = at.bg, idx = at.idx;
   // the unit's record is read beside the count that tells whether it exists
   const int2 unit = ix.funits[(int64_t)bg * ix.funits_bg + idx];
   if (idx >= ix.fcnt[bg]) return;

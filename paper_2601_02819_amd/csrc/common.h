@@ -5,6 +5,9 @@
 #include <math.h>
 #include <stdint.h>
 
+#define PHSA_HD __device__ __forceinline__
+#include "unit_map.h"
+
 namespace phsa {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));

@@ -31,9 +31,9 @@ struct Geom {
 struct IndexWs {
   int W;              // query tiles of kIndexTile rows
   int unit_tokens;    // list entries per backward work unit
-  int units_bg;       // backward units reserved per (b, g)
+  int units_bg;       // backward units reserved per (b, g), a multiple of 8
   int fpart;          // list entries per forward unit
-  int funits_bg;      // forward units reserved per (b, g)
+  int funits_bg;      // forward units reserved per (b, g), a multiple of 8
   int64_t nnz_max;    // upper bound on list entries
   int32_t *cntw;      // [R, W, T]      per-tile counts
   int32_t *toff;      // [R, W, T]      exclusive prefix of cntw over the tiles
