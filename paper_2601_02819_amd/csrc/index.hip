@@ -601,11 +601,15 @@ hipError_t launch_build_index(const Geom &g, const int32_t *sel, const IndexWs &
     const uint32_t inv = (uint32_t)(((1ull << 32) + g.ksel - 1) / g.ksel);  // pair_row
     const size_t lds = (size_t)g.T * 8 * sizeof(uint32_t) + (size_t)kIndexTile * g.ksel * sizeof(int32_t);
     const size_t lds_fill = lds + (size_t)g.T * (sizeof(int32_t) + sizeof(uint64_t));
-    // The fill's workgroups sum the counts themselves while there are few: at 32 x
-    // 128 (8k tokens) scan + fill take 10.7 + 13.7 us as two launches and 19 as
-    // one, at 64 x 256 (16k) 11.8 + 16.5 against 25.6, at 128 x 512 with 32 bg (4 x
-    // 32k) 20 + 76 against 206.
-    const bool scan = (int64_t)ix.W * g.T <= 16384;
+    // The fill's workgroups sum the counts themselves while all of them are resident
+    // at once (two per CU), so that each does it beside the others; further rounds
+    // of them would each wait for theirs.  scan + fill as two launches against one,
+    // R (b, g) x W tiles x T blocks: 8 x 64 x 256 (16k) 12 + 18 against 27 us, 16 x 32
+    // x 128 28 against 26, 32 x 16 x 64 26 against 24, 4 x 128 x 512 38 against 37;
+    // beyond 512 workgroups 32 x 32 x 128 34 against 42, 96 x 8 x 32 26 against 34, 8 x
+    // 128 x 512 44 against 62, 96 x 64 x 256 119 against 213.  W * T bounds what a
+    // workgroup reads (not measured beyond).
+    const bool scan = (int64_t)g.B * g.Hkv * ix.W <= 512 && (int64_t)ix.W * g.T <= 65536;
     timing_begin("phsa_index_count", s);
     hipLaunchKernelGGL(index_count_pairs_kernel, tiles, dim3(kScanThreads), lds, s, sel, g, ix, inv);
     timing_end(s);

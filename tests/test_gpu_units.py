@@ -24,7 +24,7 @@ def wl(name, Lq, Lk, Hq, Hkv, d, top_k, n_init=1):
     wl("unit_g4_many", 1537, 1600, 8, 2, 64, 5),
     wl("one_slot", 300, 320, 2, 1, 64, 0, n_init=0),  # Ksel = 1
     wl("tiles_33", 8300, 8320, 1, 1, 64, 3),          # 33 index tiles: the fill sums two batches of counts per block
-    wl("tiles_65", 16500, 16512, 1, 1, 64, 3),        # 65 x 258 counts: the scan kernel
+    wl("tiles_65", 16500, 16512, 1, 1, 64, 3),        # 65 tiles: three batches
     wl("blocks_1030", 130, 1030 * 64, 2, 1, 64, 6),   # 1030 blocks: three rounds of the 512-thread scan
 ], ids=lambda c: c.name)
 def test_units_match_oracle(case):
