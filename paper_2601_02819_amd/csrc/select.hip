@@ -1426,14 +1426,16 @@ static hipError_t launch_select_mfma(const Geom &g, const void *Q, const float *
     timing_end(s);
   }
   timing_begin("phsa_select", s);
-  // With fewer than the 512 workgroups of 128 rows that the chip holds at once,
-  // a workgroup's own chain (bar, appends and final rank of each wave's rows) is
-  // the kernel's duration: one row tile per wave, 64 rows per workgroup (1k
-  // rows 26 -> 16 us, 1000 rows against 320 blocks 47 -> 30 us; at 512 workgroups
-  // even, at T = 2048 2.08 ms against 1.68: a staged chunk then serves half as
-  // many rows).
-  const int64_t wgs = (int64_t)((g.Lq + 127) / 128) * g.B * g.Hkv;
-  if (g.top_k <= 16 && wgs < 512) {
+  // Where workgroups of 64 rows (one row tile per wave) are resident all at once,
+  // two per CU at d = 128 and three at d = 64, the kernel lasts as long as one of
+  // them, its own chain of chunks, bar, appends and final rank; in a second round
+  // it lasts two, and workgroups of 128 rows are ahead: a staged chunk then serves
+  // twice the rows.  64 against 128 rows, T = 256 | 2048, 2 heads of 128: 256
+  // workgroups of 128 rows 30 against 42 | 110 against 153 us, 320 of them 49
+  // against 43 | 198 against 159; 8 heads of 64, T = 2048: 384 97 against 130, 448
+  // 158 against 139.
+  const int64_t wgs = (int64_t)((g.Lq + 127) / 128) * g.B * g.Hkv;  // of 128 rows
+  if (g.top_k <= 16 && wgs <= (D == 64 ? 384 : 256)) {
     const dim3 grid((g.Lq + 63) / 64, g.B * g.Hkv);
     hipLaunchKernelGGL((select_mfma_kernel<D, G, 16, 4, false, 64, 1>), grid, dim3(256), 0, s,
                        static_cast<const bf16_t *>(Q), mh, ml, mnorm, sel, g);
