@@ -1476,18 +1476,25 @@ static hipError_t launch_select_softmax_mfma(const Geom &g, const void *Q, const
                        n / 8);
     timing_end(s);
   }
-  // two row tiles per wave where the lists fit beside two workgroups per CU
-  constexpr int RT = G >= 2 ? 2 : 1;
+  // Workgroups of 64 (token, head) pairs where they are resident all at once (two
+  // per CU; with one head per group, and with more than 16 picks, whose lists
+  // leave no room for more pairs, always), else of 128: two row tiles per wave
+  // share a chunk's fragments.  64 against 128 pairs, 2 heads of 128, T = 512 | 2048:
+  // 128 workgroups of 128 pairs 53 against 81 | 163 against 247 us, 256 63 against
+  // 84 | 189 against 256, 512 118 against 102 | 351 against 304; 4 heads of 64, T =
+  // 2048: 512 199 against 213, 1024 351 against 359.
   timing_begin("phsa_select_softmax", s);
-  if (g.top_k <= 16) {
-    constexpr int NTOK = 64 * RT / G;
-    hipLaunchKernelGGL((select_softmax_mfma_kernel<D, G, 16, RT>), dim3((g.Lq + NTOK - 1) / NTOK, g.B * g.Hkv), dim3(256),
-                       0, s, static_cast<const bf16_t *>(Q), mh, ml, mnorm, sel, g);
-  } else {
-    constexpr int NTOK = 64 / G;
-    hipLaunchKernelGGL((select_softmax_mfma_kernel<D, G, 32, 1>), dim3((g.Lq + NTOK - 1) / NTOK, g.B * g.Hkv), dim3(256),
-                       0, s, static_cast<const bf16_t *>(Q), mh, ml, mnorm, sel, g);
-  }
+  auto launch = [&](auto kmax_c, auto rt_c) {
+    constexpr int KMAX = decltype(kmax_c)::value, RT = decltype(rt_c)::value, NTOK = 64 * RT / G;
+    hipLaunchKernelGGL((select_softmax_mfma_kernel<D, G, KMAX, RT>), dim3((g.Lq + NTOK - 1) / NTOK, g.B * g.Hkv),
+                       dim3(256), 0, s, static_cast<const bf16_t *>(Q), mh, ml, mnorm, sel, g);
+  };
+  using One = std::integral_constant<int, 1>;
+  constexpr int RTM = G >= 2 ? 2 : 1;
+  const int64_t wgs = (int64_t)((g.Lq + 128 / G - 1) / (128 / G)) * g.B * g.Hkv;  // of 128 pairs
+  if (g.top_k > 16) launch(std::integral_constant<int, 32>{}, One{});
+  else if (RTM == 1 || wgs <= (D == 64 ? 512 : 256)) launch(std::integral_constant<int, 16>{}, One{});
+  else launch(std::integral_constant<int, 16>{}, std::integral_constant<int, RTM>{});
   timing_end(s);
   return hipGetLastError();
 }

@@ -45,3 +45,17 @@ def run(B, Hkv, G, d, Lq, T, top_k, window, ties, softmax_sum):
 ])
 def test_summed_logits(B, Hkv, G, d, Lq, T, top_k, window, ties):
     run(B, Hkv, G, d, Lq, T, top_k, window, ties, False)
+
+
+@pytest.mark.parametrize("ties", [False, True])
+@pytest.mark.parametrize("B,Hkv,G,d,Lq,T,top_k,window", [
+    (8, 8, 2, 128, 256, 90, 12, 0),      # 256 workgroups of 128 pairs: one tile per wave
+    (8, 8, 2, 128, 257, 90, 12, 32),     # 320: two, the last workgroup one token
+    (8, 8, 4, 64, 256, 130, 16, 0),      # 512 at d = 64: one
+    (8, 9, 4, 64, 257, 130, 5, 64),      # 648: two
+    (5, 13, 8, 128, 65, 80, 16, 0),      # 325: two
+    (8, 8, 1, 128, 700, 80, 12, 0),      # one head per group: one
+    (8, 8, 2, 64, 600, 80, 20, 0),       # more than 16 picks: one
+])
+def test_softmax_sum(B, Hkv, G, d, Lq, T, top_k, window, ties):
+    run(B, Hkv, G, d, Lq, T, top_k, window, ties, True)
