@@ -30,9 +30,6 @@
 #ifndef PHSA_SEL_NW
 #define PHSA_SEL_NW 4      // waves per selection workgroup (k <= 16)
 #endif
-#ifndef PHSA_SEL_DB
-#define PHSA_SEL_DB false  // double-buffered pass 2 (k <= 16)
-#endif
 #ifndef PHSA_SEL_SLACK
 #define PHSA_SEL_SLACK 112 // list capacity beyond 4 k entries
 #endif
@@ -842,9 +839,9 @@ __global__ __launch_bounds__(256, (KMAX > 16 && G == 1 ? 1 : 2)) void select_sof
 // representative fragment read from LDS feeds RT MFMAs, and one staged chunk of CH representatives
 // serves all rows of the workgroup.  Chunks are copied from global memory
 // straight into swizzled LDS tiles (global_load_lds); pass 1 keeps the next
-// chunk(s) in flight, pass 2 one or two (hi, lo) pairs (DB).  With k <= 16
-// the kernel runs with 4 waves and one pair: 80 KB of LDS, two workgroups per
-// CU, whose phases then overlap.
+// chunk in flight, pass 2 takes one (hi, lo) pair at a time.  With k <= 16 the
+// kernel runs with 4 waves: 80 KB of LDS, two workgroups per CU, whose phases
+// then overlap.
 // In the accumulator layout lane (q4, l16) holds, per tile, the scores of rows
 // 4 q4 + r (r = 0..3) for blocks t0 + 16 nt + l16: the 16 lanes of a
 // quarter-wave see every block of their rows, each lane a fixed residue of
@@ -959,7 +956,7 @@ __device__ __noinline__ int compact_list(float2 *lp, int n, int k, float *ks) {
   return pos;
 }
 
-template <int D, int G, int KMAXK, int NW, bool DB, int CH, int RT>
+template <int D, int G, int KMAXK, int NW, int CH, int RT>
 __global__ __launch_bounds__(NW * 64) void select_mfma_kernel(const bf16_t *__restrict__ Q,
                                                               const bf16_t *__restrict__ Mh_g,
                                                               const bf16_t *__restrict__ Ml_g,
@@ -972,15 +969,13 @@ __global__ __launch_bounds__(NW * 64) void select_mfma_kernel(const bf16_t *__re
   constexpr int KB = D / 32;
   constexpr int TILE = CH * MP;           // bf16 elements reserved per staged hi (or lo) chunk
   constexpr int TD = CH * D;              // bf16 elements of a chunk copied in (swizzled [CH][D], no padding)
-  constexpr int NBUF = DB ? 2 : 1;        // pass 2 buffers (one: two barriers per chunk)
-  constexpr int P1 = 2 * NBUF;            // pass 1 buffers (hi only): chunks in flight P1 - 1
   constexpr int VPR = D / 8, RPI = 64 / VPR, NI = CH / RPI / NW;  // 1 KB copies per wave per chunk
   constexpr int C4 = 4 * KMAXK + PHSA_SEL_SLACK;  // capacity of a 4-row list: 4 k survivors + one 64-entry append + slack
   constexpr int NGRP = NW * NR;           // lists per workgroup
   static_assert(NI >= 1 && NI * NW * RPI == CH && TD <= TILE, "chunk copies");
   static_assert(C4 >= 4 * KMAXK + 64, "list capacity");
-  // staging: pass 1 uses P1 hi chunks, pass 2 NBUF (hi, lo) pairs; the same bytes
-  __shared__ __attribute__((aligned(16))) bf16_t stg[NBUF * 2 * TILE];
+  // staging: two hi chunks in pass 1, a (hi, lo) pair in pass 2; the same bytes
+  __shared__ __attribute__((aligned(16))) bf16_t stg[2 * TILE];
   __shared__ __attribute__((aligned(16))) float2 lists[NGRP * C4];  // candidate entries; bar scratch first
   __shared__ float kth_s[NGRP * 4];
   __shared__ float2 nmax_s[NW];
@@ -1082,13 +1077,6 @@ __global__ __launch_bounds__(NW * 64) void select_mfma_kernel(const bf16_t *__re
                                        (lds_void_t *)(dst + blk * RPI * D), 16, 0, 0);
     }
   };
-  // waits until at most n of this wave's copies are outstanding (n a multiple of NI, at most 2 NI)
-  auto dma_wait_n = [&](int n) {
-    if (n >= 2 * NI) __builtin_amdgcn_s_waitcnt(0x0f70 | (2 * NI));
-    else if (n >= NI) __builtin_amdgcn_s_waitcnt(0x0f70 | NI);
-    else __builtin_amdgcn_s_waitcnt(0x0f70);
-  };
-  static_assert(2 * NI < 16, "vmcnt immediate");
   // the B fragment of 16 representatives (rows n0 .. n0 + 15) for feature slice kb
   auto frag = [&](const bf16_t *tile, int n0, int kb) { return load_bf16x8(&tile[swz<D>(n0 + l16, kb * 32 + kq)]); };
 
@@ -1101,18 +1089,18 @@ __global__ __launch_bounds__(NW * 64) void select_mfma_kernel(const bf16_t *__re
     lo_r[rr] = i < gm.Lq ? max(0, (gm.q_pos0 + i) / gm.m - gm.window / gm.m) : 0;
     top1[rr] = top2[rr] = -INFINITY;
   }
-  // P1 - 1 chunks in flight ahead of the one in use
-  for (int j = 0; j < P1 - 1 && j < nch; ++j) dma_chunk(mh_bg, j, stg + j * TD);
+  // one chunk in flight ahead of the one in use
+  if (nch > 0) dma_chunk(mh_bg, 0, stg);
   auto keep2 = [&](int rr, float v) {  // best two of the stripe (top1 >= top2)
     top2[rr] = __builtin_amdgcn_fmed3f(top1[rr], top2[rr], v);  // the middle of the three
     top1[rr] = fmaxf(top1[rr], v);
   };
   for (int c = 0; c < nch; ++c) {
-    dma_wait_n(min(P1 - 2, nch - 1 - c) * NI);  // chunk c landed (later chunks may still be in flight)
+    dma_wait();  // chunk c landed
     lds_barrier();
-    // buffer (c + P1 - 1) % P1 held chunk c - 1, which every wave finished before this barrier
-    if (c + P1 - 1 < nch) dma_chunk(mh_bg, c + P1 - 1, stg + ((c + P1 - 1) % P1) * TD);
-    const bf16_t *hb = stg + (c % P1) * TD;
+    // the other buffer held chunk c - 1, which every wave finished before this barrier
+    if (c + 1 < nch) dma_chunk(mh_bg, c + 1, stg + ((c + 1) & 1) * TD);
+    const bf16_t *hb = stg + (c & 1) * TD;
     const int t0 = gm.n_init + c * CH;
     f32x4 acc[RT][NT];
 #pragma unroll
@@ -1266,38 +1254,20 @@ __global__ __launch_bounds__(NW * 64) void select_mfma_kernel(const bf16_t *__re
     if (t0 + CH <= lo_first) appends(std::true_type{});
     else appends(std::false_type{});
   };
-  if (DB) {  // chunk c + 1 is copied into the other (hi, lo) pair while chunk c is used
-    if (nch > 0) {
-      dma_chunk(mh_bg, 0, stg);
-      dma_chunk(ml_bg, 0, stg + TD);
-    }
-    for (int c = 0; c < nch; ++c) {
-      dma_wait_n(0);
-      lds_barrier();  // chunk c landed; every wave finished chunk c - 1, whose pair is now free
-      bf16_t *cur = stg + (c & 1) * 2 * TD, *nxt = stg + ((c + 1) & 1) * 2 * TD;
-      if (c + 1 < nch) {
-        dma_chunk(mh_bg, c + 1, nxt);
-        dma_chunk(ml_bg, c + 1, nxt + TD);
-      }
-      pass2_chunk(cur, cur + TD, c);
-    }
+  for (int c = 0; c < nch; ++c) {
+    lds_barrier();  // every wave finished chunk c - 1
+    dma_chunk(mh_bg, c, stg);
+    dma_chunk(ml_bg, c, stg + TD);
+    dma_wait();
     lds_barrier();
-  } else {
-    for (int c = 0; c < nch; ++c) {
-      lds_barrier();  // every wave finished chunk c - 1
-      dma_chunk(mh_bg, c, stg);
-      dma_chunk(ml_bg, c, stg + TD);
-      dma_wait_n(0);
-      lds_barrier();
-      pass2_chunk(stg, stg + TD, c);
-    }
-    lds_barrier();
+    pass2_chunk(stg, stg + TD, c);
   }
+  lds_barrier();
 
   // ---- final: per list, split by row into the (now free) staging area, then
   // each quarter-wave ranks its row's entries and writes the row
   uint64_t *split = reinterpret_cast<uint64_t *>(stg) + wave * C4;  // this wave's scratch, as keys
-  static_assert(NW * C4 * sizeof(uint64_t) <= NBUF * 2 * TILE * sizeof(bf16_t), "split scratch");
+  static_assert(NW * C4 * sizeof(uint64_t) <= 2 * TILE * sizeof(bf16_t), "split scratch");
 #pragma unroll 1
   for (int rr = 0; rr < NR; ++rr) {
     const float2 *lp = mylists + rr * C4;
@@ -1437,15 +1407,15 @@ static hipError_t launch_select_mfma(const Geom &g, const void *Q, const float *
   const int64_t wgs = (int64_t)((g.Lq + 127) / 128) * g.B * g.Hkv;  // of 128 rows
   if (g.top_k <= 16 && wgs <= (D == 64 ? 384 : 256)) {
     const dim3 grid((g.Lq + 63) / 64, g.B * g.Hkv);
-    hipLaunchKernelGGL((select_mfma_kernel<D, G, 16, 4, false, 64, 1>), grid, dim3(256), 0, s,
+    hipLaunchKernelGGL((select_mfma_kernel<D, G, 16, 4, 64, 1>), grid, dim3(256), 0, s,
                        static_cast<const bf16_t *>(Q), mh, ml, mnorm, sel, g);
   } else if (g.top_k <= 16) {
     const dim3 grid((g.Lq + PHSA_SEL_NW * 32 - 1) / (PHSA_SEL_NW * 32), g.B * g.Hkv);
-    hipLaunchKernelGGL((select_mfma_kernel<D, G, 16, PHSA_SEL_NW, PHSA_SEL_DB, PHSA_SEL_CH, 2>), grid, dim3(PHSA_SEL_NW * 64), 0, s,
+    hipLaunchKernelGGL((select_mfma_kernel<D, G, 16, PHSA_SEL_NW, PHSA_SEL_CH, 2>), grid, dim3(PHSA_SEL_NW * 64), 0, s,
                        static_cast<const bf16_t *>(Q), mh, ml, mnorm, sel, g);
   } else {
     const dim3 grid((g.Lq + 255) / 256, g.B * g.Hkv);
-    hipLaunchKernelGGL((select_mfma_kernel<D, G, 32, 8, false, 64, 2>), grid, dim3(512), 0, s,
+    hipLaunchKernelGGL((select_mfma_kernel<D, G, 32, 8, 64, 2>), grid, dim3(512), 0, s,
                        static_cast<const bf16_t *>(Q), mh, ml, mnorm, sel, g);
   }
   timing_end(s);
