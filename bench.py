@@ -58,7 +58,7 @@ def source_hash(kernel: str) -> str:
     while it matches the hash stored with the measurement."""
     import hashlib
     h = hashlib.sha256()
-    for f in (KERNEL_SOURCE[kernel], "common.h", "launch.h"):
+    for f in (KERNEL_SOURCE[kernel], "common.h", "unit_map.h", "launch.h"):
         h.update(code_text(open(os.path.join(CSRC, f)).read()).encode())
     return h.hexdigest()[:16]
 

@@ -24,10 +24,10 @@
 // stores them as full 16-byte lanes, with non-temporal stores (only the merge
 // reads them, so they should not displace the rows and tiles the kernel reuses).
 //
-// What bounds it: the gathers and partials at 4 x 32k (15.1 GB in 2.20 ms,
-// 6.8 TB/s between the L2s and the memory side), and in small problems the
-// chain of one unit: record -> entries -> rows -> products -> stores, about 8 us
-// for a few chunks.  Short units (unit_size in api.hip) keep that chain the
+// What bounds it: memory traffic at 4 x 32k (5.2 GB read and 7.7 GB written, nearly
+// all of it partials, in 2.2 ms: 5.8 TB/s), and in small problems the chain of
+// one unit: record -> entries -> rows -> products -> stores, about 8 us for a few
+// chunks.  Short units (unit_size in api.hip) keep that chain the
 // longest thing that runs: with units of 2048 entries the list that every row
 // is on (block 0) took 75 us at 1k tokens and 258 us at 8k, against 16 and 113
 // us now.  The units of a (b, g) go to as few XCDs as a fair share allows

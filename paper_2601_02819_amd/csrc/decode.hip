@@ -10,9 +10,10 @@
 //   top-k  : one wave holds all scores in registers and takes the best one
 //            (score desc, block asc) top_k times, a wave maximum each; then it
 //            writes the sel row and leaves the slot list in LDS.
-//   attend : the selected keys, slot after slot, are dealt to the waves in
-//            groups of KG keys with NI 16-byte loads of K and of V in flight per
-//            lane; a running softmax per wave, merged in LDS into O and LSE.
+//   attend : the selected keys, slot after slot, are dealt to the waves, 32 at a
+//            time on the matrix cores (bf16) or NI 16-byte loads of K and of V per
+//            lane (float32); a running softmax per wave, merged in LDS into O and
+//            LSE.
 //
 // Both reads are bound by HBM when there are sequences enough to fill the chip
 // (64 x 32k: 370 MB in 60 us, 6.2 TB/s; 75 us as a selection and an attention
@@ -640,7 +641,7 @@ __global__ __launch_bounds__(NW * 64, (kDecodeSmall<T, G, MODE> ? 4 : 2)) void d
     float acc = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      // a wave without keys left zeros (or nothing, with factor 0): never multiply what it did not write
+      // every wave has stored its sums, zeros where it had no keys (factor 0)
       const float f = wf[w][h];
       acc = fmaf(f, sc[w * AREA + h * D + c], acc);
     }
