@@ -47,12 +47,15 @@
 // (computed with a running maximum in slot order).
 #include <math.h>
 
+#include <type_traits>
+
 #include "common.h"
 #include "launch.h"
 
 namespace phsa {
 
-template <int D, int G>
+// ANY: K and V start anywhere, not at multiples of 16 bytes.
+template <int D, int G, bool ANY = false>
 __global__ __launch_bounds__(256, 3) void attn_fwd_sparse_kernel(const bf16_t *__restrict__ Q,
                                                               const bf16_t *__restrict__ K,
                                                               const bf16_t *__restrict__ V, Geom gm, IndexWs ix,
@@ -101,8 +104,14 @@ __global__ __launch_bounds__(256, 3) void attn_fwd_sparse_kernel(const bf16_t *_
   {
     const int64_t krow0 = ((int64_t)b * gm.Lk + (int64_t)t * 64) * gm.Hkv + g;
     const int kstep = gm.Hkv * D;
-    tile_dma<D>(K + krow0 * D, [&](int r) { return r * kstep; }, Ks, wave, lane);
-    tile_dma<D>(V + krow0 * D, [&](int r) { return r * kstep; }, Vs, wave, lane);
+    const auto row_off = [&](int r) { return r * kstep; };
+    if constexpr (!ANY) {
+      tile_dma<D>(K + krow0 * D, row_off, Ks, wave, lane);
+      tile_dma<D>(V + krow0 * D, row_off, Vs, wave, lane);
+    } else {
+      tile_copy<D>(K + krow0 * D, row_off, Ks, wave, lane);
+      tile_copy<D>(V + krow0 * D, row_off, Vs, wave, lane);
+    }
   }
   bf16x8 qa[KB], qb[KB];
   fetch(e_a, qa);
@@ -272,9 +281,14 @@ template <int D, int G>
 static hipError_t launch_fwd_t(const Geom &g, const void *Q, const void *K, const void *V, void *O, float *LSE,
                                const IndexWs &ix, void *opart, float2 *ml, hipStream_t s) {
   timing_begin("phsa_attn_fwd_sparse", s);
-  hipLaunchKernelGGL((attn_fwd_sparse_kernel<D, G>), dim3((unsigned)(g.B * g.Hkv * ix.funits_bg)), dim3(256), 0, s,
-                     static_cast<const bf16_t *>(Q), static_cast<const bf16_t *>(K), static_cast<const bf16_t *>(V),
-                     g, ix, static_cast<bf16_t *>(opart), ml);
+  auto sparse = [&](auto any_c) {
+    hipLaunchKernelGGL((attn_fwd_sparse_kernel<D, G, decltype(any_c)::value>),
+                       dim3((unsigned)(g.B * g.Hkv * ix.funits_bg)), dim3(256), 0, s, static_cast<const bf16_t *>(Q),
+                       static_cast<const bf16_t *>(K), static_cast<const bf16_t *>(V), g, ix,
+                       static_cast<bf16_t *>(opart), ml);
+  };
+  if (starts_at_16(K) && starts_at_16(V)) sparse(std::false_type{});
+  else sparse(std::true_type{});
   timing_end(s);
   if (g.band) {  // the band kernel runs after the sparse one and merges every row itself
     const hipError_t e = launch_fwd_band(g, Q, K, V, ix, opart, ml, O, LSE, s);

@@ -246,6 +246,19 @@ __device__ __forceinline__ void tile_dma(const bf16_t *src, RowOff row_off, bf16
   }
 }
 
+// The same tile by way of registers, for a caller's tensor that does not start at
+// a multiple of 16 bytes, as the copies straight into LDS want it (ordinary loads
+// take any start of an element).
+template <int D, typename RowOff>
+__device__ __forceinline__ void tile_copy(const bf16_t *src, RowOff row_off, bf16_t *dst, int wave, int lane) {
+  constexpr int VPR = D / 8, RPI = 64 / VPR, NI = 64 / RPI / 4;
+#pragma unroll 1
+  for (int v = 0; v < NI; ++v) {
+    const int blk = wave * NI + v, r = blk * RPI + lane / VPR, c = (lane % VPR) ^ (r & (VPR - 1));
+    *reinterpret_cast<u32x4 *>(dst + blk * RPI * D + lane * 8) = *reinterpret_cast<const u32x4 *>(src + row_off(r) + c * 8);
+  }
+}
+
 // Waits until this wave's tile_dma copies have landed in LDS (vmcnt(0); the
 // other counters are left alone).
 __device__ __forceinline__ void dma_wait() { __builtin_amdgcn_s_waitcnt(0x0f70); }

@@ -278,6 +278,20 @@ __device__ __forceinline__ void copy_values(const bf16_t *Vb, int64_t kstep, con
   }
 }
 
+// copy_values by way of registers, for caches that do not start at a multiple of
+// 16 bytes.
+template <int D>
+__device__ __forceinline__ void copy_values_reg(const bf16_t *Vb, int64_t kstep, const int (&key0)[2], int pos,
+                                                bf16_t *Vs, int lane) {
+  constexpr int VPR = D / 8, RPI = 64 / VPR;
+#pragma unroll
+  for (int v = 0; v < 32 / RPI; ++v) {
+    const int r = v * RPI + lane / VPR, c = (lane % VPR) ^ (r & (VPR - 1));
+    const int key = min(key0[(v * RPI) >> 4] + (r & 15), pos);
+    *reinterpret_cast<u32x4 *>(Vs + v * RPI * D + lane * 8) = *reinterpret_cast<const u32x4 *>(Vb + key * kstep + c * 8);
+  }
+}
+
 // MODE 0 ranks on the summed logits of the group's heads.  MODE 1
 // (PHSA_FLAG_SELECT_SOFTMAX_SUM) keeps every head's log2 logits of the
 // complete blocks 0..cur-1 in LDS, reduces each head's log2 normaliser over
@@ -287,7 +301,8 @@ __device__ __forceinline__ void copy_values(const bf16_t *Vb, int64_t kstep, con
 // bf16 where the heads are not scored apart; the others take 8 waves with 256.
 template <typename T, int G, int MODE> constexpr bool kDecodeSmall = G <= 2 || (sizeof(T) == 2 && MODE != 1);
 
-template <typename T, int D, int G, int MODE, int NW>
+// ANY: V starts anywhere (bf16; float32 reads it into registers as it is).
+template <typename T, int D, int G, int MODE, int NW, bool ANY>
 __global__ __launch_bounds__(NW * 64, (kDecodeSmall<T, G, MODE> ? 4 : 2)) void decode_kernel(const T *__restrict__ Q, const T *__restrict__ K,
                                                            const T *__restrict__ V, const float *__restrict__ Kc,
                                                            const int32_t *__restrict__ clen,
@@ -445,7 +460,8 @@ __global__ __launch_bounds__(NW * 64, (kDecodeSmall<T, G, MODE> ? 4 : 2)) void d
       // by another path, which the order of LDS instructions does not cover
       wave_lds_sync();
       lds_wait();
-      copy_values<D>(Vb, kstep, key0, pos, Vs, lane);
+      if constexpr (!ANY) copy_values<D>(Vb, kstep, key0, pos, Vs, lane);
+      else copy_values_reg<D>(Vb, kstep, key0, pos, Vs, lane);
       f32x4 st[2];
       float mn = mrun;
 #pragma unroll
@@ -658,10 +674,10 @@ struct DecodeArgs {
   float *LSE;
 };
 
-template <typename T, int D, int G, int MODE, int NW>
+template <typename T, int D, int G, int MODE, int NW, bool ANY = false>
 static hipError_t launch_decode_w(const Geom &g, const DecodeArgs &a, int slices, hipStream_t s) {
   timing_begin("phsa_decode", s);
-  hipLaunchKernelGGL((decode_kernel<T, D, G, MODE, NW>), dim3(g.B * g.Hkv), dim3(NW * 64),
+  hipLaunchKernelGGL((decode_kernel<T, D, G, MODE, NW, ANY>), dim3(g.B * g.Hkv), dim3(NW * 64),
                      std::max(MODE == 2 ? 0 : (size_t)(MODE == 1 ? G : 1) * g.T * sizeof(float),
                               (size_t)NW * decode_wave_bytes<T, D, G>()),
                      s, static_cast<const T *>(a.Q), static_cast<const T *>(a.K), static_cast<const T *>(a.V), a.Kc,
@@ -671,15 +687,18 @@ static hipError_t launch_decode_w(const Geom &g, const DecodeArgs &a, int slices
 }
 
 // Up to one workgroup per CU they take 16 waves, beyond that 8 (two share a CU).
-template <typename T, int D, int G, int MODE>
+template <typename T, int D, int G, int MODE, bool ANY = false>
 static hipError_t launch_decode_m(const Geom &g, const DecodeArgs &a, int slices, hipStream_t s) {
   if constexpr (kDecodeSmall<T, G, MODE>)
-    if (g.B * g.Hkv <= 256) return launch_decode_w<T, D, G, MODE, 16>(g, a, slices, s);
-  return launch_decode_w<T, D, G, MODE, 8>(g, a, slices, s);
+    if (g.B * g.Hkv <= 256) return launch_decode_w<T, D, G, MODE, 16, ANY>(g, a, slices, s);
+  return launch_decode_w<T, D, G, MODE, 8, ANY>(g, a, slices, s);
 }
 
 template <typename T, int D, int G>
 static hipError_t launch_decode_g(const Geom &g, const DecodeArgs &a, hipStream_t s) {
+  if constexpr (sizeof(T) == 2)
+    if (!starts_at_16(a.V))  // a check inside the kernel took 1.1 us of 69 (64 x 32k)
+      return g.sel_mode == 1 ? launch_decode_m<T, D, G, 1, true>(g, a, 0, s) : launch_decode_m<T, D, G, 0, true>(g, a, 0, s);
   if (g.sel_mode == 1) return launch_decode_m<T, D, G, 1>(g, a, 0, s);
   // Slices of the candidate range: as many as the group's O rows hold lists of
   // (one wave ranks at most 64 entries), while the workgroups fit the CUs and a

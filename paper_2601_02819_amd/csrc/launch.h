@@ -25,6 +25,9 @@ struct Geom {
                       // fills beside K_comp so that the selection need not; NULL elsewhere
 };
 
+// Whether a caller's tensor takes 16-byte copies straight into LDS.
+inline bool starts_at_16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+
 // Index (inverted selection) workspace, carved out of the caller's buffer.
 // R = B * Hkv.  Every (b, g) has regions of its own (lists, work units, forward
 // units), so no pass needs a prefix over all of them.
