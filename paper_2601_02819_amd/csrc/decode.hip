@@ -740,13 +740,13 @@ static hipError_t launch_decode_t(const Geom &g, const DecodeArgs &a, hipStream_
 // and a ballot per wave (one thread counting them a byte at a time took the call
 // from 7 to 30 us).  When one thread per chunk added the slices' sums, those of
 // a narrow cache (2 heads of 64: 16 threads, 64 slices) took the kernel to 28 us.
-template <typename T, int D>
-__global__ __launch_bounds__(1024) void cache_append_kernel(const T *__restrict__ Kn, const T *__restrict__ Vn,
+template <typename T, int D, int NTHR>
+__global__ __launch_bounds__(NTHR) void cache_append_kernel(const T *__restrict__ Kn, const T *__restrict__ Vn,
                                                             const uint8_t *__restrict__ pn, T *__restrict__ Kcache,
                                                             T *__restrict__ Vcache, uint8_t *__restrict__ pcache,
                                                             int32_t *__restrict__ clen, float *__restrict__ Kc,
                                                             Geom gm) {
-  constexpr int VEC = 16 / sizeof(T), NTHR = 1024, U = 8;
+  constexpr int VEC = 16 / sizeof(T), U = 8;
   __shared__ float red[2][NTHR][VEC];
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
   const int pos = clen[b];
@@ -824,15 +824,31 @@ __global__ __launch_bounds__(1024) void cache_append_kernel(const T *__restrict_
   if (tid == 0) clen[b] = pos + 1;
 }
 
-template <typename T, int D>
-static hipError_t launch_cache_append_t(const Geom &g, const void *Kn, const void *Vn, const uint8_t *pn, void *Kcache,
+template <typename T, int D, int NTHR>
+static hipError_t launch_cache_append_n(const Geom &g, const void *Kn, const void *Vn, const uint8_t *pn, void *Kcache,
                                         void *Vcache, uint8_t *pcache, int32_t *clen, float *Kc, hipStream_t s) {
   timing_begin("phsa_cache_append", s);
-  hipLaunchKernelGGL((cache_append_kernel<T, D>), dim3(g.B), dim3(1024), 0, s, static_cast<const T *>(Kn),
+  hipLaunchKernelGGL((cache_append_kernel<T, D, NTHR>), dim3(g.B), dim3(NTHR), 0, s, static_cast<const T *>(Kn),
                      static_cast<const T *>(Vn), pn, static_cast<T *>(Kcache), static_cast<T *>(Vcache), pcache, clen,
                      Kc, g);
   timing_end(s);
   return hipGetLastError();
+}
+
+template <typename T, int D>
+static hipError_t launch_cache_append_t(const Geom &g, const void *Kn, const void *Vn, const uint8_t *pn, void *Kcache,
+                                        void *Vcache, uint8_t *pcache, int32_t *clen, float *Kc, hipStream_t s) {
+  // 1024 threads up to one workgroup per CU, where a completed block's chain is the
+  // call; more workgroups wait for each other's waves and LDS (64 KB at 1024
+  // threads), and most of them only copy a row.  1024 | 512 | 256 threads, 8 heads
+  // of 128 in 64-token blocks, no block completed / ragged lengths / every block
+  // completed: 256 sequences 4.3 / 7.8 / 9.0 | 4.3 / 7.7 / 9.0 | 4.1 / 9.8 / 11.1 us
+  // (32 heads: 15.3 | 16.6 | 26.1 ragged), 512 5.2 / 9.0 / 18.5 | 4.7 / 8.1 / 15.8 |
+  // 4.6 / 9.9 / 16.0, 2048 10.3 / 14.1 / 60 | 7.1 / 11.3 / 48 | 5.9 / 11.8 / 48; 2 heads
+  // of 64, 4096 sequences 15.3 / 20.5 / 89.5 | 8.8 / 11.2 / 28.2 | 6.4 / 8.1 / 17.4.
+  if (g.B <= 256) return launch_cache_append_n<T, D, 1024>(g, Kn, Vn, pn, Kcache, Vcache, pcache, clen, Kc, s);
+  if (g.B <= 512) return launch_cache_append_n<T, D, 512>(g, Kn, Vn, pn, Kcache, Vcache, pcache, clen, Kc, s);
+  return launch_cache_append_n<T, D, 256>(g, Kn, Vn, pn, Kcache, Vcache, pcache, clen, Kc, s);
 }
 
 hipError_t launch_cache_append(const Geom &g, const void *Kn, const void *Vn, const uint8_t *pn, void *Kcache,
