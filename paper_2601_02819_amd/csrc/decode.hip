@@ -78,6 +78,10 @@ __device__ __forceinline__ float wave_max_dpp(float v) {
 
 __device__ __forceinline__ float wave_min_dpp(float v) { return -wave_max_dpp(-v); }
 
+// A NaN score (a NaN or two infinities in a representative) ranks last, as -inf:
+// it compares with nothing, and its bits would order above every number.
+__device__ __forceinline__ float rank_score(float x) { return x == x ? x : -INFINITY; }
+
 // The k best of the nc candidates sc[0 .. nc) (score desc, index asc), by one
 // wave, one pick after the other: lane l holds candidates l, l + 64, ..., and
 // each round takes the wave's maximum (the lowest index among equals) out of
@@ -89,7 +93,7 @@ __device__ __noinline__ int wave_extract_k(const float *sc, int nc, int k) {
   uint32_t taken = 0;  // bit j: candidate j of this lane is out (a score may be -inf itself)
 #pragma unroll
   for (int j = 0; j < PER; ++j) {
-    v[j] = j * 64 + lane < nc ? sc[j * 64 + lane] : -INFINITY;
+    v[j] = j * 64 + lane < nc ? rank_score(sc[j * 64 + lane]) : -INFINITY;
     taken |= j * 64 + lane < nc ? 0u : 1u << j;
   }
   int mine = 0x7fffffff;
@@ -104,9 +108,8 @@ __device__ __noinline__ int wave_extract_k(const float *sc, int nc, int k) {
       bj = in ? j : bj;
     }
     const float top = wave_max_dpp(best);
-    uint64_t m = __ballot(bj >= 0 && best == top);
-    if (m == 0) m = __ballot(bj >= 0);  // scores that compare with nothing (NaN): any remaining one
-    int low = 0x7fffffff;               // the lowest index among the equals
+    const uint64_t m = __ballot(bj >= 0 && best == top);  // not empty: k <= nc, and no score is NaN
+    int low = 0x7fffffff;                                 // the lowest index among the equals
     for (uint64_t x = m; x; x &= x - 1) {
       const int l = __builtin_ctzll(x);
       low = min(low, __builtin_amdgcn_readlane(bj, l) * 64 + l);
@@ -255,7 +258,7 @@ __global__ __launch_bounds__(512) void decode_scan_kernel(const T *__restrict__ 
   if (k > 0) c = top_k_of(sc + gm.n_init + c0, n, k, lane, list_s, score);
   if (lane < gm.top_k)
     reinterpret_cast<float2 *>(O + q0)[blockIdx.x * gm.top_k + lane] =
-        make_float2(score, __int_as_float(lane < k ? gm.n_init + c0 + c : -1));
+        make_float2(rank_score(score), __int_as_float(lane < k ? gm.n_init + c0 + c : -1));
 }
 
 // LDS of one wave in the attention: its V tile (bf16: 32 keys), later its sums.
