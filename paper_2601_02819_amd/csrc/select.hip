@@ -601,8 +601,8 @@ __global__ __launch_bounds__(256, (KMAX > 16 && G == 1 ? 1 : 2)) void select_sof
     for (int r = 1; r < GL; ++r) m = fmaxf(m, a[u * GL + r] - n[u * GL + r]);
     if (G == 8) m = fmaxf(m, __shfl_xor(m, 16, 64));
     float e = 0.f;
-    if (G == 2) {  // the larger head's term is 2^0 = 1
-      e = 1.f + __builtin_amdgcn_exp2f(fminf(a[u * GL] - n[u * GL], a[u * GL + 1] - n[u * GL + 1]) - m);
+    if (G == 2) {  // the larger head's term is 2^0 = 1; a NaN (an infinite query) stays one, as in the sums below
+      e = 1.f + __builtin_amdgcn_exp2f(__builtin_elementwise_minimum(a[u * GL] - n[u * GL], a[u * GL + 1] - n[u * GL + 1]) - m);
     } else {
 #pragma unroll
       for (int r = 0; r < GL; ++r) e += __builtin_amdgcn_exp2f(a[u * GL + r] - n[u * GL + r] - m);
