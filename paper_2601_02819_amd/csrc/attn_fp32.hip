@@ -181,7 +181,8 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_fp32_kernel(const float *__r
       L = fmaf(f, wl[v][h], L);
       acc = fmaf(f, wo[v][h][c], acc);
     }
-    O[w.qrow(gm, h) + c] = L > 0.f ? acc / L : 0.f;
+    // NaN beside a NaN or +inf score; 0 where no score was a number above -inf
+    O[w.qrow(gm, h) + c] = L > 0.f ? acc / L : M == -INFINITY ? 0.f : acc * 0.f;
     if (c == 0)
       LSE[((int64_t)w.b * gm.Hq + w.g * G + h) * gm.Lq + w.i] = L > 0.f ? (M + log2f(L)) * kLn2 : -INFINITY;
   }
