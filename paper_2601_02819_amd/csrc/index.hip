@@ -27,6 +27,8 @@
 //           counts the fill's workgroups do this themselves).
 //   fill  : rebuilds the tile bitmap; an entry's place in its list is
 //           tile offset + number of lower rows in the tile that chose t.
+#include <type_traits>
+
 #include "common.h"
 #include "launch.h"
 
@@ -365,7 +367,7 @@ __global__ __launch_bounds__(kScanThreads) void index_scan_kernel(Geom gm, Index
 // ---- selections whose blocks are the index's own (64-token blocks without a
 // band, float32): kScanThreads threads per 256-row tile take the tile's (row,
 // slot) pairs, each pair on its own.  A row's entries are the valid prefix of
-// its sel row; bad_s[r] is the first slot past it.  float32 rows (every_slot) keep
+// its sel row; bad_s[r] is the first slot past it.  float32 rows (EVERY) keep
 // each valid slot, as the row-major float32 kernels do; a block listed more than
 // once is one entry that counts its copies.  (One thread per row walking
 // its slots took 12 + 20 us for count and fill at 8k tokens and 49 + 85 at 4 x 32k,
@@ -374,11 +376,11 @@ __global__ __launch_bounds__(kScanThreads) void index_scan_kernel(Geom gm, Index
 // The row of pair x (x / ks, by the reciprocal inv = ceil(2^32 / ks); x < 2^14).
 __device__ __forceinline__ int pair_row(int x, int ks, uint32_t inv) { return ks == 1 ? x : (int)__umulhi((uint32_t)x, inv); }
 
-__device__ __forceinline__ bool every_slot(const Geom &gm) { return gm.dtype != 0; }  // float32
-
 // Stages the tile's sel rows, finds bad_s and sets the tile's bitmap bm [8][T].
-// every_slot: an invalid slot is staged as -1 and bad_s stays ks; *twice_s is set
-// when a row lists a block more than once.
+// EVERY (float32): an invalid slot is staged as -1 and bad_s stays ks; *twice_s is
+// set when a row lists a block more than once.  (Chosen at run time it cost the
+// fill of a small bf16 call 0.8 of 12 us.)
+template <bool EVERY>
 __device__ __forceinline__ void pair_bitmap(uint32_t *bm, int32_t *rows_s, int *bad_s, int *twice_s,
                                             const int32_t *__restrict__ sel, const Geom &gm, int ks, uint32_t inv,
                                             int bg, int w) {
@@ -387,31 +389,32 @@ __device__ __forceinline__ void pair_bitmap(uint32_t *bm, int32_t *rows_s, int *
   const int32_t *src = sel + ((int64_t)bg * gm.Lq + (int64_t)w * kIndexTile) * ks;
   for (int x = tid; x < gm.T * 8; x += kScanThreads) bm[x] = 0u;
   if (tid < kIndexTile) bad_s[tid] = ks;
-  if (tid == 0) *twice_s = 0;
+  if (EVERY && tid == 0) *twice_s = 0;
   __syncthreads();
   for (int x = tid; x < n; x += kScanThreads) {
     const int r = pair_row(x, ks, inv), t = src[x];
     const bool ok = slot_valid(t, (gm.q_pos0 + w * kIndexTile + r) >> msh, gm.T);
-    rows_s[x] = ok ? t : -1;
-    if (!ok && !every_slot(gm)) atomicMin(&bad_s[r], x - r * ks);
+    rows_s[x] = ok || !EVERY ? t : -1;
+    if (!ok && !EVERY) atomicMin(&bad_s[r], x - r * ks);
   }
   __syncthreads();
   for (int x = tid; x < n; x += kScanThreads) {
     const int r = pair_row(x, ks, inv), t = rows_s[x];
-    if (t < 0 || x - r * ks >= bad_s[r]) continue;
+    if (EVERY ? t < 0 : x - r * ks >= bad_s[r]) continue;
     uint32_t *word = &bm[(r >> 5) * gm.T + t];
-    if (!every_slot(gm)) atomicOr(word, 1u << (r & 31));
+    if (!EVERY) atomicOr(word, 1u << (r & 31));
     else if (atomicOr(word, 1u << (r & 31)) >> (r & 31) & 1u) *twice_s = 1;
   }
   __syncthreads();
 }
 
+template <bool EVERY>
 __global__ __launch_bounds__(kScanThreads) void index_count_pairs_kernel(const int32_t *__restrict__ sel, Geom gm,
                                                                          IndexWs ix, uint32_t inv) {
   extern __shared__ uint32_t bm[];
   __shared__ int bad_s[kIndexTile], twice_s;
   const int w = blockIdx.x, bg = blockIdx.y;
-  pair_bitmap(bm, reinterpret_cast<int32_t *>(bm + 8 * gm.T), bad_s, &twice_s, sel, gm, gm.ksel, inv, bg, w);
+  pair_bitmap<EVERY>(bm, reinterpret_cast<int32_t *>(bm + 8 * gm.T), bad_s, &twice_s, sel, gm, gm.ksel, inv, bg, w);
   int32_t *dst = ix.cntw + ((int64_t)bg * ix.W + w) * gm.T;
   for (int t = threadIdx.x; t < gm.T; t += kScanThreads) {
     int c = 0;
@@ -423,7 +426,7 @@ __global__ __launch_bounds__(kScanThreads) void index_count_pairs_kernel(const i
 
 // SCAN: every workgroup sums the tile counts itself instead of reading a scan
 // kernel's prefixes (one launch less; launch_build_index has the rule).
-template <bool SCAN>
+template <bool SCAN, bool EVERY>
 __global__ __launch_bounds__(kScanThreads) void index_fill_pairs_kernel(const int32_t *__restrict__ sel, Geom gm,
                                                                         IndexWs ix, uint32_t inv, int tp) {
   extern __shared__ uint32_t bm[];
@@ -442,7 +445,7 @@ __global__ __launch_bounds__(kScanThreads) void index_fill_pairs_kernel(const in
     const int32_t *list_off = ix.off + (int64_t)bg * gm.T;
     for (int t = tid; t < gm.T; t += kScanThreads) base_s[t] = list_off[t] + tile_off[t];
   }
-  pair_bitmap(bm, rows_s, bad_s, &twice_s, sel, gm, ks, inv, bg, w);  // its barriers also publish base_s
+  pair_bitmap<EVERY>(bm, rows_s, bad_s, &twice_s, sel, gm, ks, inv, bg, w);  // its barriers also publish base_s
   for (int t = tid; t < gm.T; t += kScanThreads) {
     uint64_t pre = 0;
     int run = 0;  // at most 7 x 32 = 224 rows below the last word
@@ -459,13 +462,13 @@ __global__ __launch_bounds__(kScanThreads) void index_fill_pairs_kernel(const in
   for (int x = tid; x < n; x += kScanThreads) {
     const int r = pair_row(x, ks, inv), s = x - r * ks, t = rows_s[x];
     int p = -1;
-    if (t >= 0 && s < bad_s[r]) {
+    if (EVERY ? t >= 0 : s < bad_s[r]) {
       const int word = r >> 5;
       // lower rows of the tile that chose t: those of the lower words (a byte of pre_s) and of its own
       const uint32_t lower = reinterpret_cast<const uint8_t *>(&pre_s[t])[word];
       p = base_s[t] + (int)lower + __popc(bm[word * gm.T + t] & ((1u << (r & 31)) - 1u));
       int low = s;
-      if (every_slot(gm)) {  // the slot is not used: further copies of the block in the row
+      if (EVERY) {  // the slot is not used: further copies of the block in the row
         low = 0;
         if (twice_s)
           for (int y = r * ks; y < (r + 1) * ks; ++y) low += y != x && rows_s[y] == t;
@@ -611,7 +614,8 @@ hipError_t launch_build_index(const Geom &g, const int32_t *sel, const IndexWs &
     // workgroup reads (not measured beyond).
     const bool scan = (int64_t)g.B * g.Hkv * ix.W <= 512 && (int64_t)ix.W * g.T <= 65536;
     timing_begin("phsa_index_count", s);
-    hipLaunchKernelGGL(index_count_pairs_kernel, tiles, dim3(kScanThreads), lds, s, sel, g, ix, inv);
+    if (g.dtype == 0) hipLaunchKernelGGL(index_count_pairs_kernel<false>, tiles, dim3(kScanThreads), lds, s, sel, g, ix, inv);
+    else hipLaunchKernelGGL(index_count_pairs_kernel<true>, tiles, dim3(kScanThreads), lds, s, sel, g, ix, inv);
     timing_end(s);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (!scan) {
@@ -621,10 +625,14 @@ hipError_t launch_build_index(const Geom &g, const int32_t *sel, const IndexWs &
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     timing_begin("phsa_index_fill", s);
-    if (scan)
-      hipLaunchKernelGGL(index_fill_pairs_kernel<true>, tiles, dim3(kScanThreads), lds_fill, s, sel, g, ix, inv, tp);
-    else
-      hipLaunchKernelGGL(index_fill_pairs_kernel<false>, tiles, dim3(kScanThreads), lds_fill, s, sel, g, ix, inv, tp);
+    auto fill = [&](auto scan_c, auto every_c) {
+      hipLaunchKernelGGL((index_fill_pairs_kernel<decltype(scan_c)::value, decltype(every_c)::value>), tiles,
+                         dim3(kScanThreads), lds_fill, s, sel, g, ix, inv, tp);
+    };
+    using Yes = std::true_type;
+    using No = std::false_type;
+    if (g.dtype == 0) scan ? fill(Yes{}, No{}) : fill(No{}, No{});
+    else scan ? fill(Yes{}, Yes{}) : fill(No{}, Yes{});
     timing_end(s);
     return hipGetLastError();
   }
