@@ -1403,9 +1403,10 @@ static hipError_t launch_select_mfma(const Geom &g, const void *Q, const float *
   // twice the rows.  64 against 128 rows, T = 256 | 2048, 2 heads of 128: 256
   // workgroups of 128 rows 30 against 42 | 110 against 153 us, 320 of them 49
   // against 43 | 198 against 159; 8 heads of 64, T = 2048: 384 97 against 130, 448
-  // 158 against 139.
+  // 158 against 139.  With few blocks a short last round of the first tiles is over
+  // early: 4 heads of 64, T = 33: 408 25.0 against 27.4, 442 29.8 against 29.2.
   const int64_t wgs = (int64_t)((g.Lq + 127) / 128) * g.B * g.Hkv;  // of 128 rows
-  if (g.top_k <= 16 && wgs <= (D == 64 ? 384 : 256)) {
+  if (g.top_k <= 16 && wgs <= (D == 64 ? (g.T <= 64 ? 416 : 384) : 256)) {
     const dim3 grid((g.Lq + 63) / 64, g.B * g.Hkv);
     hipLaunchKernelGGL((select_mfma_kernel<D, G, 16, 4, 64, 1>), grid, dim3(256), 0, s,
                        static_cast<const bf16_t *>(Q), mh, ml, mnorm, sel, g);

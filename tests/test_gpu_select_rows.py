@@ -40,6 +40,8 @@ def run(B, Hkv, G, d, Lq, T, top_k, window, ties, softmax_sum):
     (8, 8, 2, 128, 500, 90, 12, 0),      # 256 tiles of 128 rows: one per wave
     (8, 8, 2, 128, 513, 90, 12, 32),     # 320: two, the last tile one row
     (8, 12, 8, 64, 400, 70, 16, 0),      # 384 at d = 64: one
+    (8, 13, 2, 64, 500, 60, 9, 0),       # 416 at d = 64, few blocks: one
+    (8, 13, 2, 64, 500, 66, 9, 0),       # 416 at d = 64: two
     (8, 8, 1, 64, 900, 130, 5, 0),       # 512 at d = 64: two, chunks past the first 64 blocks
     (5, 13, 4, 128, 600, 80, 16, 64),    # 325: two
 ])
