@@ -73,7 +73,7 @@ __global__ __launch_bounds__(256, 3) void attn_fwd_sparse_kernel(const bf16_t *_
   const UnitAt at = unit_at(blockIdx.x, gm.B * gm.Hkv, ix.funits_bg);
   const int bg = at.bg, idx = at.idx;
   // the unit's record is read beside the count that tells whether it exists
-  const int2 unit = ix.funits[(int64_t)bg * ix.funits_bg + idx];
+  const int2 unit = ix.funits[at.u];
   if (idx >= ix.fcnt[bg]) return;
   const int t = unit.x >> 16, n_ent = unit.x & 0xffff;
   const int b = bg / gm.Hkv, g = bg - b * gm.Hkv;

@@ -6,7 +6,7 @@
 namespace phsa {
 
 struct UnitAt {
-  int bg, idx;
+  int bg, idx, u;  // u = bg * per_bg + idx, known before the division
 };
 
 // Unit of workgroup lin in a grid of R * per_bg (R = B * Hkv; every (b, g) has
@@ -29,7 +29,7 @@ PHSA_HD UnitAt unit_at(int lin, int R, int per_bg) {
   const int x = lin & 7, j = lin >> 3;
   const int item = (j << (3 - lg)) | (x & ((8 >> lg) - 1));  // in the group's order
   const int first = (x >> (3 - lg)) * (R >> lg), y = item / per_bg;
-  return {first + y, item - y * per_bg};
+  return {first + y, item - y * per_bg, first * per_bg + item};
 }
 
 }  // namespace phsa

@@ -19,16 +19,17 @@ def unit_at(tmp_path_factory):
         pytest.skip("needs g++")
     d = tmp_path_factory.mktemp("unit_map")
     (d / "m.cpp").write_text('#define PHSA_HD static inline\n#include "unit_map.h"\n'
-                             'extern "C" void run(int R, int per, int *bg, int *idx) {\n'
+                             'extern "C" int run(int R, int per, int *bg, int *idx) {\n'
                              '  for (int x = 0; x < R * per; ++x) {\n'
                              '    const phsa::UnitAt a = phsa::unit_at(x, R, per);\n'
-                             '    bg[x] = a.bg;\n    idx[x] = a.idx;\n  }\n}\n')
+                             '    if (a.u != a.bg * per + a.idx) return 1;\n'
+                             '    bg[x] = a.bg;\n    idx[x] = a.idx;\n  }\n  return 0;\n}\n')
     subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-I", CSRC, "-o", str(d / "m.so"), str(d / "m.cpp")], check=True)
     f = ctypes.CDLL(str(d / "m.so")).run
 
     def at(R, per):
         bg, idx = np.empty(R * per, np.int32), np.empty(R * per, np.int32)
-        f(R, per, *(a.ctypes.data_as(ctypes.POINTER(ctypes.c_int)) for a in (bg, idx)))
+        assert not f(R, per, *(a.ctypes.data_as(ctypes.POINTER(ctypes.c_int)) for a in (bg, idx)))
         return bg, idx
 
     return at
