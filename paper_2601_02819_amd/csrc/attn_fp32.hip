@@ -24,6 +24,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "launch.h"
@@ -254,11 +255,16 @@ __device__ __forceinline__ f32x4 mfma_f32(float a, float b, const f32x4 &c) {
 //                            lane (q, j) contracting features q D/4 .. + D/4 - 1)
 //   dV^T += dO^T P, dK^T += Q^T dS: register r of P (rows 4 q + r) is the B
 //                            operand of step r, dO^T and Q^T come from LDS.
-// A key takes nothing from a row that may not see it: its weight is zero, and in a
-// chunk whose Q or dO holds an infinity or NaN, which a zero weight would not
-// stop in a product, the last two sums run row by row and leave such rows out.
+// A key takes nothing from a row that may not see it: its weight is zero.  An
+// infinity or NaN in Q or dO, which a zero weight would not stop in a product, sends
+// the unit through a second walk, whose last two sums run row by row and leave such
+// rows out.  (As a branch of the one walk these sums held registers that the products
+// need, 204 for 140 at d = 64, and a workgroup less per CU: the whole backward at 4k
+// tokens, 2 KV heads of 4 x 128, 32-token blocks, took 587 us without them, 677 with
+// the branch and 598 with the second walk; 4 KV heads of 2 x 64, 64-token blocks, 423,
+// 464 and 439.  The register bound is the workgroups per CU of the walk alone.)
 template <int D, int G, int M>
-__global__ __launch_bounds__(256) void attn_dkv_fp32_kernel(const float *__restrict__ Q, const float *__restrict__ K,
+__global__ __launch_bounds__(256, (D == 64 ? (M == 16 ? 2 : 3) : (M == 16 ? 1 : 2))) void attn_dkv_fp32_kernel(const float *__restrict__ Q, const float *__restrict__ K,
                                                             const float *__restrict__ V,
                                                             const float *__restrict__ dO,
                                                             const float *__restrict__ LSE,
@@ -296,8 +302,6 @@ __global__ __launch_bounds__(256) void attn_dkv_fp32_kernel(const float *__restr
     }
   }
   f32x4 dk[NT], dv[NT];
-#pragma unroll
-  for (int n = 0; n < NT; ++n) dk[n] = dv[n] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   f32x4 pq[NV], po[NV];
   float pl = 0.f, pd = 0.f, pt = 0.f;
@@ -318,81 +322,93 @@ __global__ __launch_bounds__(256) void attn_dkv_fp32_kernel(const float *__restr
       pp = r0 + tid < n_rows ? gm.q_pos0 + i : -1;
     }
   };
-  fetch(0);
   const float sl2 = gm.scale * kLog2e;
-  for (int r0 = 0; r0 < n_rows; r0 += ROWS) {
-    __syncthreads();
-    f32x4 z = f32x4{0.f, 0.f, 0.f, 0.f};  // 0 x (finite) stays 0
+  // one walk over the unit's chunks; false: it met an infinity or NaN (not ROWWISE)
+  auto walk = [&](auto rowwise_c) {
+    constexpr bool ROWWISE = decltype(rowwise_c)::value;
 #pragma unroll
-    for (int k = 0; k < NV; ++k) {
-      const int x = tid + 256 * k, r = x / VPR, c = (x % VPR) * 4;
-      *reinterpret_cast<f32x4 *>(&Qs[r * P + c]) = pq[k];
-      *reinterpret_cast<f32x4 *>(&Os[r * P + c]) = po[k];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) z[e] = fmaf(pq[k][e], 0.f, fmaf(po[k][e], 0.f, z[e]));
-    }
-    const uint64_t odd_m = __ballot(!(z[0] + z[1] + (z[2] + z[3]) == 0.f));
-    if (lane == 0) odd_s[wave] = odd_m != 0;
-    if (tid < ROWS) {
-      lse_s[tid] = pl;
-      dd_s[tid] = pd;
-      times_s[tid] = pt;
-      pos_s[tid] = pp;
-    }
-    __syncthreads();
-    if (r0 + ROWS < n_rows) fetch(r0 + ROWS);
-    f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f}, dp = s;
-    const float *qr = &Qs[(rt * 16 + l16) * P + q4 * F], *orow = &Os[(rt * 16 + l16) * P + q4 * F];
-#pragma unroll
-    for (int f = 0; f < F; f += 4) {
-      const f32x4 a = *reinterpret_cast<const f32x4 *>(qr + f), c = *reinterpret_cast<const f32x4 *>(orow + f);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        s = mfma_f32(a[e], kf[f + e], s);
-        dp = mfma_f32(c[e], vf[f + e], dp);
-      }
-    }
-    // lane (q, j): rows 4 q + r of the tile, key j
-    float p[4], ds[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int x = rt * 16 + q4 * 4 + r;
-      const float w = times_s[x] * __builtin_amdgcn_exp2f(fmaf(s[r], sl2, -lse_s[x]));
-      const bool sees = key <= pos_s[x];
-      p[r] = sees ? w : 0.f;
-      ds[r] = sees ? w * (dp[r] - dd_s[x]) : 0.f;
-    }
-    if (__builtin_amdgcn_readfirstlane(odd_s[0] | odd_s[1] | odd_s[2] | odd_s[3])) {
+    for (int n = 0; n < NT; ++n) dk[n] = dv[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (!ROWWISE) fetch(0);
 #pragma unroll 1
-      for (int xq = 0; xq < 4; ++xq)
+    for (int r0 = 0; r0 < n_rows; r0 += ROWS) {
+      if (ROWWISE) fetch(r0);
+      __syncthreads();
+      f32x4 z = f32x4{0.f, 0.f, 0.f, 0.f};  // 0 x (finite) stays 0
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int x = rt * 16 + xq * 4 + r;
-          const float px = __shfl(p[r], xq * 16 + l16, 64), dx = __shfl(ds[r], xq * 16 + l16, 64);
-          if (key > pos_s[x]) continue;
+      for (int k = 0; k < NV; ++k) {
+        const int x = tid + 256 * k, r = x / VPR, c = (x % VPR) * 4;
+        *reinterpret_cast<f32x4 *>(&Qs[r * P + c]) = pq[k];
+        *reinterpret_cast<f32x4 *>(&Os[r * P + c]) = po[k];
 #pragma unroll
-          for (int n = 0; n < NT; ++n) {
-            const f32x4 ov = *reinterpret_cast<const f32x4 *>(&Os[x * P + n * 16 + q4 * 4]);
-            const f32x4 qv = *reinterpret_cast<const f32x4 *>(&Qs[x * P + n * 16 + q4 * 4]);
+        for (int e = 0; e < 4; ++e) z[e] = fmaf(pq[k][e], 0.f, fmaf(po[k][e], 0.f, z[e]));
+      }
+      const uint64_t odd_m = __ballot(!(z[0] + z[1] + (z[2] + z[3]) == 0.f));
+      if (lane == 0) odd_s[wave] = odd_m != 0;
+      if (tid < ROWS) {
+        lse_s[tid] = pl;
+        dd_s[tid] = pd;
+        times_s[tid] = pt;
+        pos_s[tid] = pp;
+      }
+      __syncthreads();
+      if (!ROWWISE && r0 + ROWS < n_rows) fetch(r0 + ROWS);
+      f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f}, dp = s;
+      const float *qr = &Qs[(rt * 16 + l16) * P + q4 * F], *orow = &Os[(rt * 16 + l16) * P + q4 * F];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              dv[n][e] = fmaf(ov[e], px, dv[n][e]);
-              dk[n][e] = fmaf(qv[e], dx, dk[n][e]);
-            }
-          }
+      for (int f = 0; f < F; f += 4) {
+        const f32x4 a = *reinterpret_cast<const f32x4 *>(qr + f), c = *reinterpret_cast<const f32x4 *>(orow + f);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          s = mfma_f32(a[e], kf[f + e], s);
+          dp = mfma_f32(c[e], vf[f + e], dp);
         }
-      continue;
-    }
-    // features x keys: A = dO^T (lane: feature l16 of the tile, row 4 q + r), B = P
-#pragma unroll
-    for (int n = 0; n < NT; ++n)
+      }
+      // lane (q, j): rows 4 q + r of the tile, key j
+      float p[4], ds[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int at = (rt * 16 + q4 * 4 + r) * P + n * 16 + l16;
-        dv[n] = mfma_f32(Os[at], p[r], dv[n]);
-        dk[n] = mfma_f32(Qs[at], ds[r], dk[n]);
+        const int x = rt * 16 + q4 * 4 + r;
+        const float w = times_s[x] * __builtin_amdgcn_exp2f(fmaf(s[r], sl2, -lse_s[x]));
+        const bool sees = key <= pos_s[x];
+        p[r] = sees ? w : 0.f;
+        ds[r] = sees ? w * (dp[r] - dd_s[x]) : 0.f;
       }
-  }
+      if (ROWWISE) {
+#pragma unroll 1
+        for (int xq = 0; xq < 4; ++xq)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const int x = rt * 16 + xq * 4 + r;
+            const float px = __shfl(p[r], xq * 16 + l16, 64), dx = __shfl(ds[r], xq * 16 + l16, 64);
+            if (key > pos_s[x]) continue;
+#pragma unroll
+            for (int n = 0; n < NT; ++n) {
+              const f32x4 ov = *reinterpret_cast<const f32x4 *>(&Os[x * P + n * 16 + q4 * 4]);
+              const f32x4 qv = *reinterpret_cast<const f32x4 *>(&Qs[x * P + n * 16 + q4 * 4]);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                dv[n][e] = fmaf(ov[e], px, dv[n][e]);
+                dk[n][e] = fmaf(qv[e], dx, dk[n][e]);
+              }
+              __builtin_amdgcn_sched_barrier(0);  // a feature tile at a time: no more registers than the other walk
+            }
+          }
+        continue;
+      }
+      if (!ROWWISE && __builtin_amdgcn_readfirstlane(odd_s[0] | odd_s[1] | odd_s[2] | odd_s[3])) return false;
+      // features x keys: A = dO^T (lane: feature l16 of the tile, row 4 q + r), B = P
+#pragma unroll
+      for (int n = 0; n < NT; ++n)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int at = (rt * 16 + q4 * 4 + r) * P + n * 16 + l16;
+          dv[n] = mfma_f32(Os[at], p[r], dv[n]);
+          dk[n] = mfma_f32(Qs[at], ds[r], dk[n]);
+        }
+    }
+    return true;
+  };
+  if (__builtin_expect(!walk(std::false_type{}), 0)) walk(std::true_type{});
   // row tiles of one key tile meet in LDS, one after another; lane (q, j) holds
   // features 16 n + 4 q .. + 3 of key j
   if (RTL > 1) {
